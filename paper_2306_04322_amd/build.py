@@ -20,8 +20,11 @@ CSRC = os.path.join(PKG, "csrc")
 BUILD = os.path.join(ROOT, "_build")
 LIB = os.path.join(PKG, "libpfspec.so")
 
-SOURCES = ["pfspec.hip", "k_row_f32.hip", "k_row_f64.hip", "k_col_f32.hip", "k_col_f64.hip",
-           "k_reduce.hip", "k_fd.hip", "k_adj_f32.hip", "k_adj_f64.hip"]
+# (the slowest first: they set the build time)
+ROW_F32 = ["k_row_f32_p78.hip", "k_row_f32_p56.hip", "k_row_f32_p34.hip", "k_row_f32.hip"]
+ROW_F64 = [n.replace("f32", "f64") for n in ROW_F32]
+SOURCES = ROW_F32 + ROW_F64 + ["k_adj_f32.hip", "k_adj_f64.hip", "k_fd.hip", "k_col_f32.hip",
+                               "k_col_f64.hip", "pfspec.hip", "k_reduce.hip"]
 
 ARCH = "gfx950"
 CFLAGS = ["--offload-arch=" + ARCH, "-O3", "-std=c++17", "-fPIC", "-fno-gpu-rdc",
@@ -31,7 +34,7 @@ CFLAGS = ["--offload-arch=" + ARCH, "-O3", "-std=c++17", "-fPIC", "-fno-gpu-rdc"
 
 # The files the FP32 FS row and column kernels are compiled from.
 FS_F32_KERNEL_SOURCES = ["pf_fe.h", "pf_fft.h", "pf_kernels.h", "pf_launch.h",
-                         "k_row.inc", "k_row_f32.hip", "k_col.inc", "k_col_f32.hip"]
+                         "k_row.inc", "k_col.inc", "k_col_f32.hip"] + ROW_F32
 
 
 def source_digest(names=None):

@@ -21,9 +21,10 @@
 // derivative and forward-transforms (R2C) the right-hand-side combinations,
 // and accumulates double-precision sums.  Two forms: rowpass_kernel (one
 // wavefront per transform, rows staged in an LDS row buffer) for rows of
-// 512 and 1024 points, and xpass_kernel (one team of lanes per row, all
-// fields of the row in registers) for shorter and longer rows (the launcher
-// in k_row.inc chooses; the LDS form only where its buffer fits).
+// 512 and 1024 points and for shorter rows on small grids, and xpass_kernel
+// (one team of lanes per row, all fields of the row in registers) for the
+// other shorter rows and for longer ones (the launcher in k_row.inc chooses;
+// the LDS form only where its buffer fits).
 //
 // Column pass (col_kernel): transforms along a strided axis (y, or z in
 // 3D) for a tile of C consecutive x-spectrum columns.  Lanes are laid out
@@ -207,7 +208,8 @@ __device__ __forceinline__ void row_r2c(c2<T>* v, c2<T>* __restrict__ dst, c2<T>
 // Row pass, register form: one team of NX/(2E) lanes per row holds all F
 // fields of its row in registers (the pointwise phase needs no LDS), and the
 // x-spectra of all fields are loaded before the first transform.  Used for
-// rows of up to 256 points and from 2048 points (the launcher chooses).
+// rows of up to 256 points on large grids and from 2048 points (the launcher
+// chooses).
 // FX >= 0 fixes the flags apart from X_STORE_REAL, and FEK >= 0 the
 // free-energy kind with p = PMAX, as in rowpass_kernel below.
 template <typename T, int NX, int PMAX, int FX = -1, int FEK = -1>
@@ -383,12 +385,11 @@ __device__ __forceinline__ void wave_c2r_pre(c2<T>* v, const c2<T>* __restrict__
 // output) slot and stores its x-spectrum.  FFT exchanges inside a phase are
 // wavefront-local, so only the two phase boundaries synchronise the
 // work-group.  Usable when a transform fits one wavefront (Nx <= 2048) and
-// the row buffer fits LDS; the forward launcher takes it for 512 and 1024
-// points, the adjoint wherever it is usable (else xpass_kernel /
-// adj_row_kernel).
-// SM selects the form for grids with few rows: one row per work-group and
-// just enough wavefronts for its F transforms, which spreads a small grid
-// over more compute units than 1024-point work-groups would.
+// the row buffer fits LDS; the forward launcher's rule is in k_row.inc, the
+// adjoint takes it wherever it is usable (else adj_row_kernel).
+// SM selects the form for grids with few rows: as many rows as one wavefront
+// has room for (one where a row's F transforms fill it), which spreads a
+// small grid over more compute units than 1024-point work-groups would.
 template <typename T, int NX, int PMAX, bool SM = false>
 struct RGeom {
   static constexpr int NH = NX / 2;
@@ -405,14 +406,15 @@ struct RGeom {
   // over 4) evenly over the CU's SIMDs; measured faster at Nx = 1024 (four
   // rows) and 2048 (two rows) only.  (The forward row pass now takes the
   // register form at 2048 points; the adjoint row pass keeps this one.)
-  static constexpr int BASE_ROWS = SM ? 1 : (NX >= 1024 ? 1 : 1024 / NX);
+  static constexpr int SM_ROWS = UPW > PMAX ? 1 << ilog2(UPW / (PMAX + 1)) : 1;
+  static constexpr int BASE_ROWS = SM ? SM_ROWS : (NX >= 1024 ? 1 : 1024 / NX);
   static constexpr int MULT_WANT = NX == 2048 ? PF_ROW_MULT_2048 : NX == 1024 ? PF_ROW_ROWS_LONG : PF_ROW_MULT_SHORT;
   static constexpr bool MULTI = !SM && NX <= 2048 && sizeof(T) == 4 && PF_ROW_NW > 0 && MULT_WANT > 1 &&
                                 PF_ROW_NW * MULT_WANT <= 16 &&
                                 MULT_WANT * BASE_ROWS * ROW_BYTES <= 160 * 1024;
   static constexpr int MULT = MULTI ? MULT_WANT : 1;
   static constexpr int ROWS = BASE_ROWS * MULT;
-  static constexpr int NW = SM ? (PMAX + UPW) / UPW  // ceil((PMAX + 1) / UPW)
+  static constexpr int NW = SM ? (SM_ROWS * (PMAX + 1) + UPW - 1) / UPW
                                : (PF_ROW_NW > 0 ? PF_ROW_NW * MULT : PMAX + 1);
   static constexpr int WG = 64 * NW;
   static constexpr long LDS_BYTES = long(ROWS) * ROW_BYTES;

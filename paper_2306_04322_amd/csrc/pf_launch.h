@@ -16,6 +16,7 @@ template <typename T> struct AdjArgs;
 template <typename T> struct FdArgs;
 
 template <typename T> int row_launch(int nx, int p, const XArgs<T>& a, hipStream_t s);
+template <typename T, int P> int row_launch_exact(int nx, const XArgs<T>& a, hipStream_t s);
 template <typename T> int adj_row_launch(int nx, int p, const AdjArgs<T>& a, hipStream_t s);
 template <typename T> int col_launch(int n, int nouter, const ColArgs<T>& a, hipStream_t s);
 template <typename T> int fd_launch(int which, int p, const FdArgs<T>& a, hipStream_t s);
