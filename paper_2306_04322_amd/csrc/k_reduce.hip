@@ -13,7 +13,7 @@ namespace pf {
 template <int W>
 __global__ void __launch_bounds__(256) reduce_kernel(const double* __restrict__ partials, int n,
                                                      double* __restrict__ out, double s0, double s1,
-                                                     double s2, double s3, int accumulate) {
+                                                     double s2, double s3) {
   constexpr int B = 256, U = 8;
   __shared__ double red[4 * 4];
   double acc[4] = {0.0, 0.0, 0.0, 0.0};
@@ -36,18 +36,18 @@ __global__ void __launch_bounds__(256) reduce_kernel(const double* __restrict__ 
   if (threadIdx.x == 0) {
     const double sc[4] = {s0, s1, s2, s3};
 #pragma unroll
-    for (int i = 0; i < W; ++i) out[i] = (accumulate ? out[i] : 0.0) + acc[i] * sc[i];
+    for (int i = 0; i < W; ++i) out[i] = acc[i] * sc[i];
   }
 }
 
 int reduce_launch(const double* partials, int n, int width, double* out, const double* scale4,
-                  int accumulate, hipStream_t s) {
+                  hipStream_t s) {
   if (width == 2)
     hipLaunchKernelGGL(reduce_kernel<2>, dim3(1), dim3(256), 0, s, partials, n, out, scale4[0],
-                       scale4[1], scale4[2], scale4[3], accumulate);
+                       scale4[1], scale4[2], scale4[3]);
   else if (width == 4)
     hipLaunchKernelGGL(reduce_kernel<4>, dim3(1), dim3(256), 0, s, partials, n, out, scale4[0],
-                       scale4[1], scale4[2], scale4[3], accumulate);
+                       scale4[1], scale4[2], scale4[3]);
   else
     return -1;
   return 1;

@@ -603,9 +603,11 @@ rowpass_kernel(XArgs<T> a) {
 //   q0 = <b_c, df/dc(u^n)>,  q1 = <e_c, c^(n+1) - mean(c)>,
 //   q2 = sum_i <a_i, df/deta_i(u^n)>,  q3 = sum_i <e_i, eta_i^(n+1)>
 // go to partials[block][4] (e_c has zero mean, so removing the held mean of
-// c changes nothing in exact arithmetic and keeps the sum well conditioned);
-// optionally lambda^n is R2C-transformed (the first transform of the next
-// adjoint step) into b_out.
+// c changes nothing in exact arithmetic and keeps the sum well conditioned).
+// A block adds to its own record of the steps before unless `first`, so a
+// segment needs one reduction: one per step took 4.0 us of a 22.6 us adjoint
+// step at 512^2, F = 3, FP32.  Optionally lambda^n is R2C-transformed (the
+// first transform of the next adjoint step) into b_out.
 template <typename T>
 struct AdjArgs {
   const c2<T>* s_in;
@@ -619,9 +621,18 @@ struct AdjArgs {
   long long fs_real, fs_spec;
   long long nyo;  // offset of the Nyquist values within an x-spectrum field
   int rows, Sx, F, do_fwd;
+  int first;  // first adjoint step of a segment: start the partial sums
   FeParams<T> fe;
   T dtM, dtL;
 };
+
+// This block's record of the parameter-gradient sums (q valid in thread 0).
+template <typename T>
+__device__ __forceinline__ void adj_record(const AdjArgs<T>& a, const double* q) {
+  double* rec = a.partials + 4 * (long long)blockIdx.x;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) rec[k] = a.first ? q[k] : rec[k] + q[k];
+}
 
 template <typename T, int NX, int PMAX>
 struct AGeom {
@@ -633,8 +644,8 @@ struct AGeom {
   static constexpr int REGION = lds_span(NH) + 1;
 };
 
-// FIXF: F = PMAX + 1 at compile time.
-template <typename T, int NX, int PMAX, bool FIXF = false>
+// (the order-parameter count is PMAX)
+template <typename T, int NX, int PMAX>
 __global__ void __attribute__((amdgpu_flat_work_group_size(1, AGeom<T, NX, PMAX>::WG)))
 adj_row_kernel(AdjArgs<T> a) {
   using G = AGeom<T, NX, PMAX>;
@@ -649,7 +660,7 @@ adj_row_kernel(AdjArgs<T> a) {
   const bool active = row < a.rows;
   const long long rrow = active ? row : 0;
   c2<T>* my = lds + team * G::REGION;
-  const int F = FIXF ? PMAX + 1 : a.F;
+  constexpr int F = PMAX + 1;
   const int p = F - 1;
   Twiddles<T, G::NH, E> tws;
   tws.load(t, a.twx, 2);
@@ -730,10 +741,7 @@ adj_row_kernel(AdjArgs<T> a) {
     }
   }
   block_sum<4>(q, red);
-  if (threadIdx.x == 0) {
-#pragma unroll
-    for (int k = 0; k < 4; ++k) a.partials[4 * blockIdx.x + k] = q[k];
-  }
+  if (threadIdx.x == 0) adj_record(a, q);
   if (a.do_fwd) {
 #pragma unroll
     for (int f = 0; f < FB; ++f)
@@ -744,14 +752,13 @@ adj_row_kernel(AdjArgs<T> a) {
 }
 
 // Adjoint row pass, one wavefront per transform (the forward row pass's
-// structure and geometry).  Slots: 0 = e_c, 1 = b_c, 2 + i = e_i; the
-// pointwise phase overwrites slots 0 and 2 + i with lambda^n for the
-// forward transforms of phase 3.
-// FIXF: F = PMAX + 1 at compile time.
-template <typename T, int NX, int PMAX, bool FIXF = false>
-__global__ void __attribute__((amdgpu_flat_work_group_size(1, RGeom<T, NX, PMAX>::WG)))
+// structure and geometry, SM included).  Slots: 0 = e_c, 1 = b_c, 2 + i =
+// e_i; the pointwise phase overwrites slots 0 and 2 + i with lambda^n for the
+// forward transforms of phase 3.  The order-parameter count is PMAX.
+template <typename T, int NX, int PMAX, bool SM>
+__global__ void __attribute__((amdgpu_flat_work_group_size(1, RGeom<T, NX, PMAX, SM>::WG)))
 adjrow_kernel(AdjArgs<T> a) {
-  using G = RGeom<T, NX, PMAX>;
+  using G = RGeom<T, NX, PMAX, SM>;
   constexpr int NH = G::NH, E = G::E, TEAM = G::TEAM, UPW = G::UPW, ROWS = G::ROWS;
   constexpr int NW = G::NW, SL = G::SLOTS, WG = G::WG, SC = G::SLOT_C;
   static_assert(G::FITS, "adjoint row pass v2 does not fit this size");
@@ -763,7 +770,7 @@ adjrow_kernel(AdjArgs<T> a) {
   const int unit = lane / TEAM;
   const int t = lane - unit * TEAM;
   const int row0 = blockIdx.x * ROWS;
-  const int F = FIXF ? PMAX + 1 : a.F;
+  constexpr int F = PMAX + 1;
   const int p = F - 1;
   Twiddles<T, NH, E> tws;
   tws.load(t, a.twx, 2);
@@ -866,10 +873,7 @@ adjrow_kernel(AdjArgs<T> a) {
     }
   }
   block_sum<4>(q, red);
-  if (tid == 0) {
-#pragma unroll
-    for (int k = 0; k < 4; ++k) a.partials[4 * blockIdx.x + k] = q[k];
-  }
+  if (tid == 0) adj_record(a, q);
   __syncthreads();
 
   // phase 3: R2C of lambda^n (slots 0 and 2 + i) for the next adjoint step
@@ -1235,13 +1239,5 @@ struct FdArgs {
   double ix, iy, iz;  // 1 / dx_d
   FeParams<T> fe;
 };
-
-// Single work-group fixed-order sum of `n` records of `width` doubles:
-// out[i] = scale[i] * sum_r partials[r * width + i]  (added to out[i] when
-// `accumulate` is set).
-__global__ void __launch_bounds__(256) reduce_kernel(const double* __restrict__ partials, int n,
-                                                     int width, double* __restrict__ out,
-                                                     double s0, double s1, double s2, double s3,
-                                                     int accumulate);
 
 }  // namespace pf

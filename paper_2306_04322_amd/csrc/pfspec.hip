@@ -266,10 +266,10 @@ pf_status col(pf_handle* h, ColArgs<T>& a, int axis, int* nblk) {
 }
 
 pf_status reduce(pf_handle* h, int n, int width, double* out, double s0, double s1, double s2,
-                 double s3, int accumulate = 0) {
+                 double s3) {
   const double sc[4] = {s0, s1, s2, s3};
   const int pi = prof_begin(h, PROF_RED);
-  const int g = reduce_launch(partials(h), n, width, out, sc, accumulate, h->stream);
+  const int g = reduce_launch(partials(h), n, width, out, sc, h->stream);
   prof_end(h, pi);
   if (g < 0) return fail(PF_ERR_UNSUPPORTED, "reduction: record width must be 2 or 4");
   return check_launch("reduction");
@@ -514,6 +514,7 @@ pf_status adjoint_run(pf_handle* h, double dt, long long k, const T* u0, T* lam,
   x.b_out = specB<T>(h);
   x.flags = X_LOAD_REAL | X_FWD_RAW;
   PF_TRY(row<T>(h, x, nullptr));
+  int nb = 0;  // records of the adjoint row pass
   for (long long n = k - 1; n >= 0; --n) {
     ColArgs<T> a = cargs<T>(h, dt);
     a.src = specB<T>(h);
@@ -550,16 +551,17 @@ pf_status adjoint_run(pf_handle* h, double dt, long long k, const T* u0, T* lam,
     r.nyo = h->nyo;
     r.F = h->F;
     r.do_fwd = n > 0 ? 1 : 0;
+    r.first = n == k - 1 ? 1 : 0;
     r.fe = fe_params<T>(h);
     r.dtM = T(dt * h->M);
     r.dtL = T(dt * h->L);
     const int pi = prof_begin(h, PROF_ADJ);
-    const int nb = adj_row_launch<T>(h->nx, h->p, r, h->stream);
+    nb = adj_row_launch<T>(h->nx, h->p, r, h->stream);
     prof_end(h, pi);
     if (nb < 0) return fail(PF_ERR_UNSUPPORTED, "adjoint row pass: unsupported Nx");
     PF_TRY(check_launch("adjoint row pass"));
-    PF_TRY(reduce(h, nb, 4, acc, 1, 1, 1, 1, n == k - 1 ? 0 : 1));
   }
+  PF_TRY(reduce(h, nb, 4, acc, 1, 1, 1, 1));
   double q[4];
   if (hipMemcpyAsync(q, acc, sizeof(q), hipMemcpyDeviceToHost, h->stream) != hipSuccess ||
       hipStreamSynchronize(h->stream) != hipSuccess)
