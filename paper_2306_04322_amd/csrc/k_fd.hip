@@ -2,51 +2,27 @@
 // 7-point periodic Laplacian, every right-hand side at time t) and the
 // forward-difference free-energy sums.
 //
-// The two step kernels give each thread V consecutive points along x, read
-// as one vector of up to 16 bytes (V = 4 float or 2 double on large grids,
-// fewer on small ones): each field's centre values and its y / z neighbours
-// arrive as one vector load each, the x neighbours inside the vector come
-// from registers and only the two at its ends are extra scalar loads, so a
-// field costs 5 (2D) or 7 (3D) loads per V points instead of per point.
-// The y and z neighbours are rows that neighbouring work-groups also read;
-// on grids whose neighbour rows or planes fit in L2, each XCD takes a
-// contiguous band of the grid so those re-reads stay in its own L2.  On
+// Most grids take a fused step (fd2_fused_kernel, fd3_march_kernel,
+// fd3_tile_kernel): one launch per step, mu = df/dc - kappa_c lap(c) kept on
+// the chip.  The other 3D grids (fd_fused has the rule) take two kernels with
+// mu in memory between them.
+//
+// Every kernel gives a thread V consecutive points along x, read as one vector
+// of up to 16 bytes (V = 4 float or 2 double on large grids, fewer on small
+// ones): each field's centre values and its y / z neighbours arrive as one
+// vector load each, the x neighbours inside the vector come from registers
+// and only the two at its ends are extra scalar loads, so a field costs 5
+// (2D) or 7 (3D) loads per V points instead of per point.  The y and z
+// neighbours are rows that neighbouring work-groups also read; each XCD takes
+// a contiguous band of the grid so those re-reads stay in its own L2.  On
 // larger 3D grids each thread instead marches along z over a few planes and
 // keeps its neighbour planes in registers, and a work-group stages the
-// current plane of its rows (plus one halo row on each side) in LDS for the
-// y and x neighbours.  The energy kernel keeps one thread per point.
-// Periodic wrap uses power-of-two masks instead of ghost layers.
+// current plane of its rows (plus halo rows) in LDS for the y and x
+// neighbours.  Periodic wrap uses power-of-two masks instead of ghost layers.
 #include "pf_kernels.h"
 #include "pf_launch.h"
 
 namespace pf {
-
-struct Nb {
-  long long xm, xp, ym, yp, zm, zp;
-};
-
-template <typename T>
-__device__ __forceinline__ Nb neighbours(const FdArgs<T>& a, long long i) {
-  const int x = int(i & (a.nx - 1));
-  const int y = int((i >> a.lx) & (a.ny - 1));
-  const int z = int(i >> (a.lx + a.ly));
-  const long long row = i - x;
-  const long long plane = (long long)a.nx * a.ny;
-  Nb n;
-  n.xm = row + ((x - 1) & (a.nx - 1));
-  n.xp = row + ((x + 1) & (a.nx - 1));
-  const long long zoff = (long long)z * plane;
-  n.ym = zoff + (long long)((y - 1) & (a.ny - 1)) * a.nx + x;
-  n.yp = zoff + (long long)((y + 1) & (a.ny - 1)) * a.nx + x;
-  if (a.ndim == 3) {
-    const long long rest = (long long)y * a.nx + x;
-    n.zm = (long long)((z - 1) & (a.nz - 1)) * plane + rest;
-    n.zp = (long long)((z + 1) & (a.nz - 1)) * plane + rest;
-  } else {
-    n.zm = n.zp = i;
-  }
-  return n;
-}
 
 // V consecutive points of one row, loaded and stored as one aligned vector
 // (V * sizeof(T) <= 16 bytes).
@@ -114,13 +90,30 @@ __device__ __forceinline__ NbV neighbours_vec(const FdArgs<T>& a, long long i0) 
   return n;
 }
 
-// Laplacian of field v at the V points of the vector (centre values cv),
-// in the same operation order as the per-point form.
+// Laplacian of field v at the V points of the vector (centre values cv) in
+// 2D, and in 3D.
 template <typename T, int V>
-__device__ __forceinline__ void lap_vec(const T* __restrict__ v, const FdVec<T, V>& cv, const NbV& n,
-                                        const FdArgs<T>& a, T* out) {
+__device__ __forceinline__ void lap_vec2(const T* __restrict__ v, const FdVec<T, V>& cv, const NbV& n,
+                                         const FdArgs<T>& a, T* out) {
   const FdVec<T, V> ym = ld_vec<T, V>(v + n.ym), yp = ld_vec<T, V>(v + n.yp);
   const T xl = v[n.xl], xr = v[n.xr];
+#pragma unroll
+  for (int k = 0; k < V; ++k) {
+    const T c = cv.v[k];
+    const T left = k == 0 ? xl : cv.v[k - 1];
+    const T right = k == V - 1 ? xr : cv.v[k + 1];
+    out[k] = (right - T(2) * c + left) * a.ix2 + (yp.v[k] - T(2) * c + ym.v[k]) * a.iy2;
+  }
+}
+
+template <typename T, int V>
+__device__ __forceinline__ void lap_vec3(const T* __restrict__ v, const FdVec<T, V>& cv, const NbV& n,
+                                         const FdArgs<T>& a, T* out) {
+  const FdVec<T, V> ym = ld_vec<T, V>(v + n.ym), yp = ld_vec<T, V>(v + n.yp);
+  const T xl = v[n.xl], xr = v[n.xr];
+  // (always true here: the branch keeps the compiler from moving the loads of
+  // all fields to the top, 256 x 128^2, F = 5, FP32 two-kernel step 49.0 ->
+  // 44.4 us)
   FdVec<T, V> zm, zp;
   if (a.ndim == 3) {
     zm = ld_vec<T, V>(v + n.zm);
@@ -177,7 +170,7 @@ __global__ void __launch_bounds__(256) fd_mu_kernel(FdArgs<T> a, int bands) {
     for (int j = 0; j < PMAX; ++j) ge[j][k] = g[j];
   }
   T l[V], o[V];
-  lap_vec<T, V>(a.in, cc, n, a, l);
+  lap_vec3<T, V>(a.in, cc, n, a, l);
 #pragma unroll
   for (int k = 0; k < V; ++k) o[k] = gc[k] - a.kc * l[k];
   st_vec<T, V>(a.mu + i0, o);
@@ -185,7 +178,7 @@ __global__ void __launch_bounds__(256) fd_mu_kernel(FdArgs<T> a, int bands) {
   for (int j = 0; j < PMAX; ++j)
     if (j < p) {
       const T* e = a.in + (j + 1) * a.P;
-      lap_vec<T, V>(e, ce[j], n, a, l);
+      lap_vec3<T, V>(e, ce[j], n, a, l);
 #pragma unroll
       for (int k = 0; k < V; ++k) o[k] = ce[j].v[k] - a.dtL * (ge[j][k] - a.ke * l[k]);
       st_vec<T, V>(a.out + (j + 1) * a.P + i0, o);
@@ -201,7 +194,7 @@ __global__ void __launch_bounds__(256) fd_c_kernel(FdArgs<T> a, int bands) {
   const FdVec<T, V> cm = ld_vec<T, V>(a.mu + i0);
   const FdVec<T, V> c = ld_vec<T, V>(a.in + i0);
   T l[V], o[V];
-  lap_vec<T, V>(a.mu, cm, n, a, l);
+  lap_vec3<T, V>(a.mu, cm, n, a, l);
 #pragma unroll
   for (int k = 0; k < V; ++k) o[k] = c.v[k] + a.dtM * l[k];
   st_vec<T, V>(a.out + i0, o);
@@ -507,6 +500,338 @@ __global__ void __launch_bounds__(FD_ZL_WG) fd_c_zl_kernel(FdArgs<T> a, int zb) 
   }
 }
 
+// Laplacian with the y neighbours one row up and down in an LDS tile (`me`:
+// this thread's row, row pitch nx) and the z neighbours in registers.
+template <typename T, int V>
+__device__ __forceinline__ void fd_lap_rows(const T* __restrict__ me, int nx, int x0, int xm, int xp,
+                                            const FdVec<T, V>& zm, const FdVec<T, V>& cv,
+                                            const FdVec<T, V>& zp, const FdArgs<T>& a, T* out) {
+  const FdVec<T, V> vm = *reinterpret_cast<const FdVec<T, V>*>(me - nx + x0);
+  const FdVec<T, V> vp = *reinterpret_cast<const FdVec<T, V>*>(me + nx + x0);
+  const T xl = me[xm], xr = me[xp];
+#pragma unroll
+  for (int k = 0; k < V; ++k) {
+    const T c = cv.v[k];
+    const T left = k == 0 ? xl : cv.v[k - 1];
+    const T right = k == V - 1 ? xr : cv.v[k + 1];
+    T r = (right - T(2) * c + left) * a.ix2 + (vp.v[k] - T(2) * c + vm.v[k]) * a.iy2;
+    r += (zp.v[k] - T(2) * c + zm.v[k]) * a.iz2;
+    out[k] = r;
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Fused step: mu stays on the chip.  A work-group owns a tile of rows and
+// computes mu on them and on the halo the Laplacian of mu reads, so one
+// launch reads the F fields and writes the F fields (2F instead of 2F + 3
+// arrays through memory, and one launch instead of two).
+//
+// Points in 2D and in the marching form: thread row rr = 0 .. T - 1 of a tile
+// holds grid row y0 - 1 + rr; rows 1 .. T - 2 are the tile's own, the first
+// and last only supply mu.  Every thread takes V consecutive x points.
+
+// mu at one point of a 2D grid (the tile's left and right edge columns).
+template <typename T, int P>
+__device__ __forceinline__ T fd_mu_point(const FdArgs<T>& a, int x, int y) {
+  const T* c = a.in;
+  const long long row = (long long)y * a.nx;
+  const T cc = c[row + x];
+  const T xl = c[row + ((x - 1) & (a.nx - 1))], xr = c[row + ((x + 1) & (a.nx - 1))];
+  const T ym = c[(long long)((y - 1) & (a.ny - 1)) * a.nx + x];
+  const T yp = c[(long long)((y + 1) & (a.ny - 1)) * a.nx + x];
+  T eta[P], ge[P], gc;
+#pragma unroll
+  for (int j = 0; j < P; ++j) eta[j] = a.in[(j + 1) * a.P + row + x];
+  fe_grad<T, P, -1, P>(a.fe, P, cc, eta, gc, ge);
+  const T l = (xr - T(2) * cc + xl) * a.ix2 + (yp - T(2) * cc + ym) * a.iy2;
+  return gc - a.kc * l;
+}
+
+// 2D.  The tile is FD2_LANES vectors wide (or the whole row if that is
+// shorter) and FD2_ROWS - 2 rows high.  The neighbours of the fields come
+// from the caches as in fd_mu_kernel; mu goes through LDS, whose two columns
+// beyond the tile's edges are filled by lanes of the two halo rows (which
+// have no order parameters to advance).
+constexpr int FD2_ROWS = 8;
+constexpr int FD2_LANES = 64;  // threads per row of a tile
+
+template <typename T, int P, int V>
+__global__ void __launch_bounds__(FD2_ROWS * FD2_LANES) fd2_fused_kernel(FdArgs<T> a, int lanes, int xtiles, int ntiles) {
+  constexpr int PITCH = FD2_LANES * V + 2 * V;  // columns -1 .. 64 V at offset V
+  __shared__ __align__(16) T mu[FD2_ROWS * PITCH];
+  const unsigned b = (blockIdx.x & 7u) * (gridDim.x >> 3) + (blockIdx.x >> 3);  // contiguous band per XCD
+  if (int(b) >= ntiles) return;
+  const int yt = int(b) / xtiles;
+  const int xt = int(b) - yt * xtiles;
+  const int rr = int(threadIdx.x) / lanes;
+  const int lane = int(threadIdx.x) - rr * lanes;
+  const int y0 = yt * (FD2_ROWS - 2);
+  const int y = (y0 - 1 + rr) & (a.ny - 1);
+  const int xl0 = lane * V;                 // x within the tile
+  const int x0 = xt * lanes * V + xl0;
+  const bool own = rr >= 1 && rr <= FD2_ROWS - 2 && y0 - 1 + rr < a.ny;
+  const long long i0 = (long long)y * a.nx + x0;
+  NbV n;
+  n.ym = (long long)((y - 1) & (a.ny - 1)) * a.nx + x0;
+  n.yp = (long long)((y + 1) & (a.ny - 1)) * a.nx + x0;
+  n.xl = i0 - x0 + ((x0 - 1) & (a.nx - 1));
+  n.xr = i0 - x0 + ((x0 + V) & (a.nx - 1));
+  n.zm = n.zp = i0;
+  T* mrow = mu + rr * PITCH + V;
+
+  const FdVec<T, V> cc = ld_vec<T, V>(a.in + i0);
+  FdVec<T, V> ce[P];
+#pragma unroll
+  for (int j = 0; j < P; ++j) ce[j] = ld_vec<T, V>(a.in + (j + 1) * a.P + i0);
+  T l[V], m[V], gc[V], ge[P][V];
+  lap_vec2<T, V>(a.in, cc, n, a, l);
+#pragma unroll
+  for (int k = 0; k < V; ++k) {
+    T eta[P], g[P];
+#pragma unroll
+    for (int j = 0; j < P; ++j) eta[j] = ce[j].v[k];
+    fe_grad<T, P, -1, P>(a.fe, P, cc.v[k], eta, gc[k], g);
+#pragma unroll
+    for (int j = 0; j < P; ++j) ge[j][k] = g[j];
+    m[k] = gc[k] - a.kc * l[k];
+  }
+  st_vec<T, V>(mrow + xl0, m);
+  if (xtiles > 1) {
+    // edge columns: row 0's lanes the left ones, the last row's the right
+    const int e = lane + 1;  // thread row whose edge this lane fills
+    if (e <= FD2_ROWS - 2) {
+      const int ye = (y0 - 1 + e) & (a.ny - 1);
+      const int xb = xt * lanes * V;
+      if (rr == 0) mu[e * PITCH + V - 1] = fd_mu_point<T, P>(a, (xb - 1) & (a.nx - 1), ye);
+      if (rr == FD2_ROWS - 1) mu[e * PITCH + V + lanes * V] = fd_mu_point<T, P>(a, (xb + lanes * V) & (a.nx - 1), ye);
+    }
+  }
+  if (own) {
+    T o[V];
+#pragma unroll
+    for (int j = 0; j < P; ++j) {
+      lap_vec2<T, V>(a.in + (j + 1) * a.P, ce[j], n, a, l);
+#pragma unroll
+      for (int k = 0; k < V; ++k) o[k] = ce[j].v[k] - a.dtL * (ge[j][k] - a.ke * l[k]);
+      st_vec<T, V>(a.out + (j + 1) * a.P + i0, o);
+    }
+  }
+  __syncthreads();
+  if (own) {
+    const FdVec<T, V> um = *reinterpret_cast<const FdVec<T, V>*>(mrow - PITCH + xl0);
+    const FdVec<T, V> up = *reinterpret_cast<const FdVec<T, V>*>(mrow + PITCH + xl0);
+    const int w = lanes * V;
+    const T xl = xtiles > 1 ? mrow[xl0 - 1] : mrow[(xl0 - 1) & (w - 1)];
+    const T xr = xtiles > 1 ? mrow[xl0 + V] : mrow[(xl0 + V) & (w - 1)];
+    T o[V];
+#pragma unroll
+    for (int k = 0; k < V; ++k) {
+      const T left = k == 0 ? xl : m[k - 1];
+      const T right = k == V - 1 ? xr : m[k + 1];
+      const T lm = (right - T(2) * m[k] + left) * a.ix2 + (up.v[k] - T(2) * m[k] + um.v[k]) * a.iy2;
+      o[k] = cc.v[k] + a.dtM * lm;
+    }
+    st_vec<T, V>(a.out + i0, o);
+  }
+}
+
+// 3D, large grids.  A work-group of WG threads owns all x of R = rows - 2 grid
+// rows and marches over zb planes, with the planes q - 1, q, q + 1 of every
+// field (PREF: also q + 2, loaded an iteration ahead) and mu of q - 2, q - 1, q
+// in registers; plane q of the fields (one halo row on each side, two for c)
+// and the planes q - 1 and q of mu are in LDS for the y and x neighbours.
+// Iteration q advances eta of plane q and c of plane q - 1.  Bound by memory:
+// 256^3, F = 5, FP32 138 us per step (671 MB read and written once, 4.9 TB/s)
+// against 176 us of the two kernels (872 MB); FP64 244 against 392 us.
+template <typename T, int P, int V, int WG, bool PREF>
+__global__ void __launch_bounds__(WG) fd3_march_kernel(FdArgs<T> a, int zb, int rows, int ntiles) {
+  extern __shared__ __align__(16) unsigned char fd_lds_raw[];
+  const int nx = a.nx;
+  const int tpr = nx / V;
+  T* lc = reinterpret_cast<T*>(fd_lds_raw);  // c: thread rows -1 .. rows
+  T* le = lc + (rows + 2) * nx;              // eta_j: thread rows 0 .. rows - 1 each
+  T* lm = le + P * rows * nx;                // mu: two planes of the same
+  const unsigned b = (blockIdx.x & 7u) * (gridDim.x >> 3) + (blockIdx.x >> 3);  // contiguous eighth per XCD
+  const int R = rows - 2;
+  const int ytiles = (a.ny + R - 1) / R;
+  if (int(b) >= ntiles) return;  // work-group uniform
+  const int zt = int(b) / ytiles;
+  const int z0 = zt * zb;
+  const int y0 = (int(b) - zt * ytiles) * R;
+  const int rr = int(threadIdx.x) / tpr;
+  const int x0 = (int(threadIdx.x) - rr * tpr) * V;
+  const int y = (y0 - 1 + rr) & (a.ny - 1);
+  const bool own = rr >= 1 && rr <= R && y0 - 1 + rr < a.ny;
+  const bool top = rr == 0, bot = rr == rows - 1;
+  const long long plane = (long long)nx * a.ny;
+  const long long rest = (long long)y * nx + x0;
+  const long long halo = (long long)((y + (top ? -1 : 1)) & (a.ny - 1)) * nx + x0;  // c row beyond the halo
+  const int mz = a.nz - 1;
+  const int xm = (x0 - 1) & (nx - 1), xp = (x0 + V) & (nx - 1);
+  T* myc = lc + (rr + 1) * nx;
+  T* mye = le + rr * nx;
+
+  FdVec<T, V> m[P + 1], c[P + 1], n[P + 1], nn[P + 1];
+  FdVec<T, V> hc;        // c of the row beyond the halo (first and last thread row)
+  FdVec<T, V> mua, mub;  // mu of planes q - 2 and q - 1
+#pragma unroll
+  for (int k = 0; k < V; ++k) mua.v[k] = mub.v[k] = T(0);
+  m[0] = ld_vec<T, V>(a.in + ((z0 - 2) & mz) * plane + rest);
+#pragma unroll
+  for (int f = 0; f <= P; ++f) c[f] = ld_vec<T, V>(a.in + f * a.P + ((z0 - 1) & mz) * plane + rest);
+#pragma unroll
+  for (int f = 1; f <= P; ++f) m[f] = c[f];  // (not used: eta of plane z0 - 1 is not advanced)
+#pragma unroll
+  for (int f = 0; f <= P; ++f) n[f] = ld_vec<T, V>(a.in + f * a.P + (z0 & mz) * plane + rest);
+  hc = ld_vec<T, V>(a.in + ((z0 - 1) & mz) * plane + halo);
+  for (int i = 0; i < zb + 2; ++i) {
+    const int q = z0 - 1 + i;
+    const long long zq = (q & mz) * plane;
+    if (!PREF && i > 0) {
+      const long long zn = ((q + 1) & mz) * plane + rest;
+#pragma unroll
+      for (int f = 0; f <= P; ++f) n[f] = ld_vec<T, V>(a.in + f * a.P + zn);
+    }
+    *reinterpret_cast<FdVec<T, V>*>(myc + x0) = c[0];
+#pragma unroll
+    for (int j = 0; j < P; ++j) *reinterpret_cast<FdVec<T, V>*>(mye + j * rows * nx + x0) = c[j + 1];
+    if (top) *reinterpret_cast<FdVec<T, V>*>(myc - nx + x0) = hc;
+    if (bot) *reinterpret_cast<FdVec<T, V>*>(myc + nx + x0) = hc;
+    if (PREF) {
+      const long long zn = ((q + 2) & mz) * plane + rest;
+#pragma unroll
+      for (int f = 0; f <= P; ++f) nn[f] = ld_vec<T, V>(a.in + f * a.P + zn);
+    }
+    if (top || bot) hc = ld_vec<T, V>(a.in + ((q + 1) & mz) * plane + halo);
+    __syncthreads();
+    T gc[V], ge[P][V];
+#pragma unroll
+    for (int k = 0; k < V; ++k) {
+      T eta[P], g[P];
+#pragma unroll
+      for (int j = 0; j < P; ++j) eta[j] = c[j + 1].v[k];
+      fe_grad<T, P, -1, P>(a.fe, P, c[0].v[k], eta, gc[k], g);
+#pragma unroll
+      for (int j = 0; j < P; ++j) ge[j][k] = g[j];
+    }
+    FdVec<T, V> mu;
+    T l[V], o[V];
+    fd_lap_rows<T, V>(myc, nx, x0, xm, xp, m[0], c[0], n[0], a, l);
+#pragma unroll
+    for (int k = 0; k < V; ++k) mu.v[k] = gc[k] - a.kc * l[k];
+    T* lmq = lm + (i & 1) * rows * nx + rr * nx;
+    *reinterpret_cast<FdVec<T, V>*>(lmq + x0) = mu;
+    if (own && i >= 1 && i <= zb && q < a.nz) {
+#pragma unroll
+      for (int j = 0; j < P; ++j) {
+        fd_lap_rows<T, V>(mye + j * rows * nx, nx, x0, xm, xp, m[j + 1], c[j + 1], n[j + 1], a, l);
+#pragma unroll
+        for (int k = 0; k < V; ++k) o[k] = c[j + 1].v[k] - a.dtL * (ge[j][k] - a.ke * l[k]);
+        st_vec_nt<T, V>(a.out + (j + 1) * a.P + zq + rest, o);
+      }
+    }
+    if (own && i >= 2 && q - 1 < a.nz) {
+      // the other plane of mu, written in the iteration before
+      fd_lap_rows<T, V>(lm + ((i + 1) & 1) * rows * nx + rr * nx, nx, x0, xm, xp, mua, mub, mu, a, l);
+#pragma unroll
+      for (int k = 0; k < V; ++k) o[k] = m[0].v[k] + a.dtM * l[k];
+      st_vec_nt<T, V>(a.out + ((q - 1) & mz) * plane + rest, o);
+    }
+    __syncthreads();
+    mua = mub;
+    mub = mu;
+#pragma unroll
+    for (int f = 0; f <= P; ++f) {
+      m[f] = c[f];
+      c[f] = n[f];
+      if (PREF) n[f] = nn[f];
+    }
+  }
+}
+
+// 3D, small grids with rows of at most 32 vectors: a tile of MY x MZ rows
+// (all x) and the rows next to it in y and z, whose threads only supply mu.
+// The fields' neighbours come from the caches as in fd_mu_kernel, mu goes
+// through LDS.  One pass with one barrier: these grids are bound by latency
+// and launches, so the mu of the halo rows computed twice costs less than a
+// second kernel.
+template <typename T, int P, int V, int MY, int MZ>
+__global__ void __launch_bounds__(1024) fd3_tile_kernel(FdArgs<T> a, int ytiles, int ntiles) {
+  constexpr int MM = MY * MZ;
+  extern __shared__ __align__(16) unsigned char fd_lds_raw[];
+  T* mu = reinterpret_cast<T*>(fd_lds_raw);  // [MM + 2 MY + 2 MZ][nx]
+  const unsigned b = (blockIdx.x & 7u) * (gridDim.x >> 3) + (blockIdx.x >> 3);  // contiguous eighth per XCD
+  if (int(b) >= ntiles) return;  // work-group uniform
+  const int nx = a.nx;
+  const int tpr = nx / V;
+  const int zt = int(b) / ytiles;
+  const int id = int(threadIdx.x) / tpr;
+  const int x0 = (int(threadIdx.x) - id * tpr) * V;
+  const bool own = id < MM;
+  const int h = id - MM;
+  int my, mz;
+  if (own) {
+    my = id % MY;
+    mz = id / MY;
+  } else if (h < 2 * MY) {
+    my = h % MY;
+    mz = h < MY ? -1 : MZ;
+  } else {
+    my = h < 2 * MY + MZ ? -1 : MY;
+    mz = (h - 2 * MY) % MZ;
+  }
+  const int y = ((int(b) - zt * ytiles) * MY + my) & (a.ny - 1);
+  const int z = (zt * MZ + mz) & (a.nz - 1);
+  const long long i0 = ((long long)z * a.ny + y) * nx + x0;
+  const NbV n = neighbours_vec<T, V>(a, i0);
+  const FdVec<T, V> cc = ld_vec<T, V>(a.in + i0);
+  FdVec<T, V> ce[P];
+#pragma unroll
+  for (int j = 0; j < P; ++j) ce[j] = ld_vec<T, V>(a.in + (j + 1) * a.P + i0);
+  T l[V], o[V], m[V], ge[P][V];
+  lap_vec3<T, V>(a.in, cc, n, a, l);
+#pragma unroll
+  for (int k = 0; k < V; ++k) {
+    T eta[P], g[P], gc;
+#pragma unroll
+    for (int j = 0; j < P; ++j) eta[j] = ce[j].v[k];
+    fe_grad<T, P, -1, P>(a.fe, P, cc.v[k], eta, gc, g);
+#pragma unroll
+    for (int j = 0; j < P; ++j) ge[j][k] = g[j];
+    m[k] = gc - a.kc * l[k];
+  }
+  T* row = mu + id * nx;
+  st_vec<T, V>(row + x0, m);
+  if (own) {
+#pragma unroll
+    for (int j = 0; j < P; ++j) {
+      lap_vec3<T, V>(a.in + (j + 1) * a.P, ce[j], n, a, l);
+#pragma unroll
+      for (int k = 0; k < V; ++k) o[k] = ce[j].v[k] - a.dtL * (ge[j][k] - a.ke * l[k]);
+      st_vec<T, V>(a.out + (j + 1) * a.P + i0, o);
+    }
+  }
+  __syncthreads();
+  if (own) {
+    const int ym = my > 0 ? id - 1 : MM + 2 * MY + mz;
+    const int yp = my < MY - 1 ? id + 1 : MM + 2 * MY + MZ + mz;
+    const int zm = mz > 0 ? id - MY : MM + my;
+    const int zp = mz < MZ - 1 ? id + MY : MM + MY + my;
+    const FdVec<T, V> um = ld_vec<T, V>(mu + ym * nx + x0), up = ld_vec<T, V>(mu + yp * nx + x0);
+    const FdVec<T, V> wm = ld_vec<T, V>(mu + zm * nx + x0), wp = ld_vec<T, V>(mu + zp * nx + x0);
+    const T xl = row[(x0 - 1) & (nx - 1)], xr = row[(x0 + V) & (nx - 1)];
+#pragma unroll
+    for (int k = 0; k < V; ++k) {
+      const T left = k == 0 ? xl : m[k - 1];
+      const T right = k == V - 1 ? xr : m[k + 1];
+      T r = (right - T(2) * m[k] + left) * a.ix2 + (up.v[k] - T(2) * m[k] + um.v[k]) * a.iy2;
+      r += (wp.v[k] - T(2) * m[k] + wm.v[k]) * a.iz2;
+      o[k] = cc.v[k] + a.dtM * r;
+    }
+    st_vec<T, V>(a.out + i0, o);
+  }
+}
+
 // partials[block] = {sum f(u), sum_d (dc/dx_d)^2, sum_i sum_d (deta_i/dx_d)^2, sum c}
 // with forward differences, accumulated in double.  Each thread takes the V
 // consecutive x points of one vector and adds them in increasing x.  Every
@@ -576,9 +901,6 @@ static int fd_vec_width(long long P) {
   return 1;
 }
 
-#ifndef PF_FD_ZMARCH
-#define PF_FD_ZMARCH 1  // 3D grids without bands: threads march along z
-#endif
 #ifndef PF_FD_ZLDS
 #define PF_FD_ZLDS 1  // marching kernels with the current plane staged in LDS
 #endif
@@ -586,14 +908,12 @@ static int fd_vec_width(long long P) {
 #define PF_FD_ZB 8  // planes per marching thread
 #endif
 
-// XCD bands pay while the three neighbour rows (2D) or planes (3D) of all F
-// fields fit in half of one XCD's 4 MiB L2; beyond that (3D 256^3) the plain
-// round-robin order, which sweeps the whole GPU through the grid together
-// and shares the neighbour planes through the last-level cache, is faster.
+// The two-kernel step (3D): XCD bands pay while the three neighbour planes of
+// all F fields fit in half of one XCD's 4 MiB L2; beyond that the threads
+// march along z.
 template <typename T>
 static int fd_bands(const FdArgs<T>& a) {
-  const long long span = (a.ndim == 3 ? (long long)a.nx * a.ny : (long long)a.nx) * sizeof(T);
-  return 3LL * a.F * span <= (2LL << 20) ? 1 : 0;
+  return 3LL * a.F * a.nx * a.ny * (long long)sizeof(T) <= (2LL << 20) ? 1 : 0;
 }
 
 template <typename T, int PMAX, int V>
@@ -601,7 +921,7 @@ static int fd_go_v(int which, const FdArgs<T>& a, hipStream_t s) {
   const long long nv = a.P / V;  // nx >= 8 is a multiple of V
   const bool full = a.F == PMAX + 1;  // the mu kernel's p fixed at compile time
   const int bands = fd_bands(a);
-  if (PF_FD_ZMARCH && a.ndim == 3 && !bands) {
+  if (!bands) {
     const int zb = a.nz < PF_FD_ZB ? a.nz : PF_FD_ZB;  // both powers of two
     // LDS-staged form: tiles of R >= 2 rows that divide Ny, with the plane
     // tiles of all F fields small enough for three work-groups per compute
@@ -637,6 +957,105 @@ static int fd_go_v(int which, const FdArgs<T>& a, hipStream_t s) {
   return grid;
 }
 
+template <typename T, int P, int V>
+static int fd2_fused(const FdArgs<T>& a, hipStream_t s) {
+  const int tpr = a.nx / V;
+  const int lanes = tpr < FD2_LANES ? tpr : FD2_LANES;
+  const int xtiles = tpr / lanes;
+  const int ntiles = xtiles * ((a.ny + FD2_ROWS - 3) / (FD2_ROWS - 2));
+  const int grid = (ntiles + 7) / 8 * 8;
+  hipLaunchKernelGGL((fd2_fused_kernel<T, P, V>), dim3(grid), dim3(FD2_ROWS * lanes), 0, s, a, lanes, xtiles, ntiles);
+  return grid;
+}
+
+// The 3D step by tiles: MY x MZ rows per work-group.
+template <typename T, int P, int V, int MY, int MZ>
+static int fd3_tile_go(const FdArgs<T>& a, hipStream_t s) {
+  const int ytiles = a.ny / MY;  // MY and MZ are powers of two of at most 8, like ny and nz at least
+  const int ntiles = ytiles * (a.nz / MZ);
+  const int rows = MY * MZ + 2 * MY + 2 * MZ;
+  const int grid = (ntiles + 7) / 8 * 8;
+  hipLaunchKernelGGL((fd3_tile_kernel<T, P, V, MY, MZ>), dim3(grid), dim3(rows * (a.nx / V)),
+                     size_t(rows) * a.nx * sizeof(T), s, a, ytiles, ntiles);
+  return grid;
+}
+
+// The 3D step by marching; 0 where a tile would have fewer than three rows of
+// its own or does not fit LDS.
+template <typename T, int P, int V, int WG, bool PREF>
+static int fd3_march(const FdArgs<T>& a, hipStream_t s) {
+  const int tpr = a.nx / V;
+  int rows = WG / tpr;
+  if (rows > a.ny + 2) rows = a.ny + 2;
+  const size_t lds = (size_t(rows) * (P + 3) + 2) * a.nx * sizeof(T);
+  if (rows < 5 || lds > (160u << 10)) return 0;
+  const int R = rows - 2;
+  const int ytiles = (a.ny + R - 1) / R;
+  // as many z blocks as the chip has slots for work-groups, of 8 planes at least
+  int nzb = 256 * (1024 / WG) / ytiles;
+  if (nzb > a.nz / 8) nzb = a.nz / 8;
+  if (nzb < 1) nzb = 1;
+  const int zb = (a.nz + nzb - 1) / nzb;
+  const int ntiles = ytiles * ((a.nz + zb - 1) / zb);
+  const int grid = (ntiles + 7) / 8 * 8;
+  hipLaunchKernelGGL((fd3_march_kernel<T, P, V, WG, PREF>), dim3(grid), dim3(rows * tpr), lds, s, a, zb, rows, ntiles);
+  return grid;
+}
+
+// One step in one launch; 0 where the two-kernel step is taken.
+// 2D: always fused (1024^2, F = 5, FP32 14.9 -> 11.8 us per step, 256^2 6.9 ->
+// 3.6, 4096^2 220 -> 169; FP64 22.6 -> 19.4, 7.4 -> 4.3, 407 -> 309).
+// 3D, from PF_FD3_MARCH_MB of fields (half of that where the planes of all
+// fields take at most 12 registers, which leaves room for the prefetch):
+// marching, in 512-lane work-groups with prefetch where a float row fits 64
+// lanes, else in 768-lane ones (256^3, F = 5, FP32 138 against 159 us; 512 x
+// 256 x 256 has rows for the latter only).  Below that the marching
+// work-groups are too few (128^3, F = 5, FP32 28.5 us against 25.9 of the two
+// kernels).
+// 3D, up to PF_FD3_TILE_MB of fields, or 128-point float rows with at most
+// four order parameters: tiles (32^3, F = 5, FP32 7.4 -> 3.9 us, 64^3 9.3 ->
+// 6.1, 128^3 25.9 -> 24.9; but 64 x 128^2, 21 MB: 16.3 -> 17.4; FP64 64^3 10.1
+// -> 7.4, 32 x 128^2, 21 MB: 15.1 -> 17.7).  64-point double rows with more
+// than five order parameters spill (64^3, p = 8: 14.2 -> 23.7 us) and stay
+// with the two kernels.
+#ifndef PF_FD3_MARCH_MB
+#define PF_FD3_MARCH_MB 96
+#endif
+#ifndef PF_FD3_TILE_MB
+#define PF_FD3_TILE_MB 11
+#endif
+template <typename T, int P>
+static int fd_fused(const FdArgs<T>& a, hipStream_t s) {
+  constexpr int VMAX = 16 / int(sizeof(T));
+  if (a.ndim == 2) {
+    const int v = fd_vec_width<T>(a.P);
+    if constexpr (VMAX == 4) {
+      if (v == 4) return fd2_fused<T, P, 4>(a, s);
+    }
+    return v == 2 ? fd2_fused<T, P, 2>(a, s) : fd2_fused<T, P, 1>(a, s);
+  }
+  constexpr int VM = P > 4 ? VMAX / 2 : VMAX;  // vectors that leave room in registers
+  constexpr int words = (P + 1) * VM * int(sizeof(T)) / 4;
+  const long long mb = ((long long)a.F * a.P * sizeof(T)) >> 20;
+  if (mb >= (words <= 12 ? PF_FD3_MARCH_MB / 2 : PF_FD3_MARCH_MB)) {
+    if constexpr (sizeof(T) == 4 && words > 12) {
+      if (a.nx / VM <= 64) return fd3_march<T, P, VM, 512, true>(a, s);
+    }
+    return fd3_march<T, P, VM, 768, (words <= 12)>(a, s);
+  }
+  if constexpr (VMAX == 4 && P <= 4) {
+    if (a.nx == 128) return fd3_tile_go<T, P, 4, 4, 4>(a, s);
+  }
+  if (mb >= PF_FD3_TILE_MB) return 0;
+  if (a.nx <= 8) return fd3_tile_go<T, P, 1, 8, 8>(a, s);   // 96 rows of 8 lanes
+  if (a.nx <= 16) return fd3_tile_go<T, P, 1, 4, 8>(a, s);  // 56 of 16
+  if (a.nx <= 32) return fd3_tile_go<T, P, 1, 4, 4>(a, s);  // 32 of 32
+  if constexpr (sizeof(T) == 4 || P <= 5) {
+    if (a.nx <= 64) return fd3_tile_go<T, P, 2, 4, 4>(a, s);
+  }
+  return 0;
+}
+
 template <typename T, int PMAX>
 static int fd_go(int which, const FdArgs<T>& a, hipStream_t s) {
   if (which < 2) {
@@ -669,6 +1088,30 @@ static int fd_dispatch(int which, int p, const FdArgs<T>& a, hipStream_t s) {
   if (p <= 4) return fd_go<T, 4>(which, a, s);
   if (p <= 8) return fd_go<T, 8>(which, a, s);
   return -1;
+}
+
+template <typename T>
+static int fd_fused_dispatch(int p, const FdArgs<T>& a, hipStream_t s) {
+  switch (p) {
+    case 1: return fd_fused<T, 1>(a, s);
+    case 2: return fd_fused<T, 2>(a, s);
+    case 3: return fd_fused<T, 3>(a, s);
+    case 4: return fd_fused<T, 4>(a, s);
+    case 5: return fd_fused<T, 5>(a, s);
+    case 6: return fd_fused<T, 6>(a, s);
+    case 7: return fd_fused<T, 7>(a, s);
+    case 8: return fd_fused<T, 8>(a, s);
+    default: return -1;
+  }
+}
+
+template <>
+int fd_fused_launch<float>(int p, const FdArgs<float>& a, hipStream_t s) {
+  return fd_fused_dispatch<float>(p, a, s);
+}
+template <>
+int fd_fused_launch<double>(int p, const FdArgs<double>& a, hipStream_t s) {
+  return fd_fused_dispatch<double>(p, a, s);
 }
 
 template <>

@@ -408,8 +408,10 @@ pf_status fd_run(pf_handle* h, double dt, long long nsteps) {
     a.in = cur;
     a.out = nxt;
     int pi = prof_begin(h, PROF_FD);
-    fd_launch<T>(0, h->p, a, h->stream);
-    fd_launch<T>(1, h->p, a, h->stream);
+    if (fd_fused_launch<T>(h->p, a, h->stream) == 0) {
+      fd_launch<T>(0, h->p, a, h->stream);
+      fd_launch<T>(1, h->p, a, h->stream);
+    }
     prof_end(h, pi);
     PF_TRY(check_launch("FD step"));
     T* t = cur;
