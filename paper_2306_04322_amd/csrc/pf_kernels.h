@@ -2,14 +2,14 @@
 //
 // Data layout in HBM (complex values interleaved re/im):
 //   real fields   [F][Nz][Ny][Nx]            element type T
-//   x-spectra     [G][Nz][Ny][Sx] + [G][Nz][Ny] c2<T>: row r holds the
-//                                            real-to-complex transform along x
-//                                            of row r, values kx = 0 .. Nx/2 - 1
-//                                            at row stride Sx (128-byte
-//                                            multiple); the Nyquist values
-//                                            kx = Nx/2 of all rows follow as one
-//                                            array (offset nyo in the field),
-//                                            contiguous along y
+//   x-spectra     G fields of c2<T>: value kx (0 .. Nx/2 - 1) of row r at
+//                 r rs + koff(kx); the Nyquist values kx = Nx/2 of all rows
+//                 follow as one array (offset nyo in the field), contiguous
+//                 along y.  Row-major: koff(kx) = kx, rs = Sx (a 128-byte
+//                 multiple).  Tiled (2D, long columns): tiles of KTile columns
+//                 (32 bytes) one after the other, each [Ny][KTile], so a
+//                 column work-group reads and writes contiguous memory and a
+//                 row work-group of R rows pieces of 32 R bytes.
 // A "row" is one (z, y) line along x; rows = Ny * Nz.  Keeping the Nyquist
 // column apart lets the strided passes cover kx < Nx/2 with full tiles and
 // the Nyquist column with a few items that take many outer rows at once
@@ -47,6 +47,15 @@
 #endif
 #ifndef PF_COL_CB_LONG_F64
 #define PF_COL_CB_LONG_F64 2  // columns per tile, double, transform length >= 512
+#endif
+#ifndef PF_COL_X_FROM
+#define PF_COL_X_FROM 2048
+#endif
+#ifndef PF_COL_CX_F32
+#define PF_COL_CX_F32 2
+#endif
+#ifndef PF_COL_CX_F64
+#define PF_COL_CX_F64 1
 #endif
 #ifndef PF_COL_MIN_WAVES
 #define PF_COL_MIN_WAVES 1  // register budget of the column pass (waves per SIMD)
@@ -106,6 +115,54 @@ __device__ __forceinline__ T recip(T x) {
   else return T(1) / x;
 }
 
+// Columns of a tile of the tiled x-spectrum layout, and the offset of column k
+// within its row (ts: tile stride; ts = KTile gives the row-major koff = k).
+template <typename T>
+struct KTile {
+  static constexpr int LOG = sizeof(T) == 4 ? 2 : 1;
+  static constexpr int N = 1 << LOG;
+};
+template <typename T>
+__device__ __forceinline__ unsigned koff(int k, int ts) {
+  return unsigned(k >> KTile<T>::LOG) * unsigned(ts) + unsigned(k & (KTile<T>::N - 1));
+}
+
+// Offsets of the values kx = t + TEAM m of one lane in its row's x-spectrum
+// and of their mirrors NH - kx, added to `base`.  LIN: the layout is row-major
+// (known at compile time: 1024^2, F = 5, FP32 step 33.0 -> 31.6 us).
+template <typename T, int NH, int E, bool LIN = false>
+struct RowMap {
+  static constexpr int TEAM = NH / E;
+  static constexpr bool STEP = TEAM % KTile<T>::N == 0;
+  unsigned lo, hi, step;  // offset of m = 0, of its mirror, and per m
+  int t, ts;
+  unsigned base;
+  __device__ __forceinline__ RowMap(int t_, int ts_, unsigned base_) : t(t_), ts(ts_), base(base_) {
+    lo = base + koff<T>(t, ts);
+    hi = base + koff<T>(NH - t, ts);
+    step = unsigned(TEAM / KTile<T>::N) * unsigned(ts);
+  }
+  __device__ __forceinline__ unsigned at(int m) const {
+    if constexpr (LIN) return base + t + TEAM * m;
+    else if constexpr (STEP) return lo + m * step;
+    else return base + koff<T>(t + TEAM * m, ts);
+  }
+  __device__ __forceinline__ unsigned mirror(int m) const {  // (not for kx = 0)
+    if constexpr (LIN) return base + NH - t - TEAM * m;
+    else if constexpr (STEP) return hi - m * step;
+    else return base + koff<T>(NH - t - TEAM * m, ts);
+  }
+};
+
+// Row-pass block of the launch's block b: with the tiled layout XCD x takes the
+// x-th contiguous eighth of the rows, so the rows whose pieces share a 128-byte
+// line meet in one L2 (4096^2 FP32 row pass 463 -> 302 us with 32-byte pieces).
+template <typename T>
+__device__ __forceinline__ int row_block(int ts) {
+  const unsigned b = blockIdx.x, g = gridDim.x;
+  return ts != KTile<T>::N && (g & 7u) == 0 ? int((b & 7u) * (g >> 3) + (b >> 3)) : int(b);
+}
+
 template <typename T>
 struct XArgs {
   const T* u_in;
@@ -117,20 +174,25 @@ struct XArgs {
   long long fs_real;  // field stride of real arrays (elements)
   long long fs_spec;  // field stride of x-spectra (complex elements)
   long long nyo;      // offset of the Nyquist values within an x-spectrum field
-  int rows, Sx, F, flags;
+  int rows, rs, ts, F, flags;  // rs, ts: row and tile stride of the x-spectra
   FeParams<T> fe;
   T dtL;
 };
 
 // Row pass geometry for a real length NX.
-template <typename T, int NX, int PMAX>
+// TL: for the tiled layout.
+template <typename T, int NX, int PMAX, bool TL = false>
 struct XGeom {
   static constexpr int NH = NX / 2;
   static constexpr int EW = (sizeof(T) == 8 && NX >= PF_XROW_E8_F64_MIN && PMAX <= 4) ? 8
                           : (sizeof(T) == 8 || PMAX > 4) ? 4 : 8;
   static constexpr int E = NH < EW ? NH : EW;
   static constexpr int TEAM = NH / E;
-  static constexpr int ROWS = TEAM >= 64 ? 1 : 64 / TEAM;
+  // one wavefront, or one row where a row takes more; with the tiled layout
+  // 256 lanes (two 2048-point float rows, pieces of 64 bytes: 2048^2, F = 5
+  // 59 us, as fast as row-major; row-major the second row costs 30 -> 33 us on
+  // 2048 x 1024, where one-row work-groups balance better)
+  static constexpr int ROWS = TEAM >= 64 ? (TL && TEAM < 256 ? 256 / TEAM : 1) : 64 / TEAM;
   static constexpr int WG = ROWS * TEAM;
   static constexpr int REGION = lds_span(NH) + 1;  // LDS complex values per team
   // register budget of the fixed-flag instantiations: two work-groups per
@@ -145,10 +207,10 @@ struct XGeom {
 // overlap.
 template <typename T, int NX, int E>
 __device__ __forceinline__ void row_load(c2<T>* v, c2<T>& xn, const c2<T>* __restrict__ src,
-                                         const c2<T>* __restrict__ nyq, bool active, int t) {
-  constexpr int TEAM = NX / 2 / E;
+                                         const RowMap<T, NX / 2, E>& rm, const c2<T>* __restrict__ nyq,
+                                         bool active, int t) {
 #pragma unroll
-  for (int m = 0; m < E; ++m) v[m] = active ? src[t + TEAM * m] : mk<T>(T(0), T(0));
+  for (int m = 0; m < E; ++m) v[m] = active ? src[rm.at(m)] : mk<T>(T(0), T(0));
   xn = (active && t == 0) ? *nyq : mk<T>(T(0), T(0));
 }
 
@@ -178,10 +240,10 @@ __device__ __forceinline__ void row_c2r(c2<T>* v, c2<T> xn, int t, c2<T>* my,
 }
 
 // R2C of one row held as v[m] = (x[2k], x[2k+1]); writes X[0..NH-1] to dst
-// and X[NH] to *nyq.
+// (at the offsets of rm) and X[NH] to *nyq.
 template <typename T, int NX, int E>
-__device__ __forceinline__ void row_r2c(c2<T>* v, c2<T>* __restrict__ dst, c2<T>* __restrict__ nyq,
-                                        bool active, int t,
+__device__ __forceinline__ void row_r2c(c2<T>* v, c2<T>* __restrict__ dst, const RowMap<T, NX / 2, E>& rm,
+                                        c2<T>* __restrict__ nyq, bool active, int t,
                                         c2<T>* my, const LaneTwiddles<T, NX / 2, E>& lt,
                                         const Twiddles<T, NX / 2, E>& tws) {
   constexpr int NH = NX / 2;
@@ -199,7 +261,7 @@ __device__ __forceinline__ void row_r2c(c2<T>* v, c2<T>* __restrict__ dst, c2<T>
     const c2<T> d = sub<T>(Z, Zc);  // 2 i B_k
     const c2<T> B2 = mk<T>(d.y, -d.x);  // 2 B_k
     const c2<T> WB = cmul<T>(B2, lt.w[m]);
-    if (active) dst[k] = mk<T>(T(0.5) * (s.x + WB.x), T(0.5) * (s.y + WB.y));
+    if (active) dst[rm.at(m)] = mk<T>(T(0.5) * (s.x + WB.x), T(0.5) * (s.y + WB.y));
     if (k == 0 && active) *nyq = mk<T>(T(0.5) * (s.x - B2.x), T(0.5) * (s.y - B2.y));
   }
   __syncthreads();
@@ -212,21 +274,27 @@ __device__ __forceinline__ void row_r2c(c2<T>* v, c2<T>* __restrict__ dst, c2<T>
 // chooses).
 // FX >= 0 fixes the flags apart from X_STORE_REAL, and FEK >= 0 the
 // free-energy kind with p = PMAX, as in rowpass_kernel below.
-template <typename T, int NX, int PMAX, int FX = -1, int FEK = -1>
-__global__ void __attribute__((amdgpu_flat_work_group_size(1, XGeom<T, NX, PMAX>::WG),
-                               amdgpu_waves_per_eu(FX >= 0 ? XGeom<T, NX, PMAX>::MIN_WAVES : 1)))
+template <typename T, int NX, int PMAX, int FX = -1, int FEK = -1, bool TL = false>
+__global__ void __attribute__((amdgpu_flat_work_group_size(1, XGeom<T, NX, PMAX, TL>::WG),
+                               amdgpu_waves_per_eu(FX >= 0 ? XGeom<T, NX, PMAX, TL>::MIN_WAVES : 1)))
 xpass_kernel(XArgs<T> a) {
-  using G = XGeom<T, NX, PMAX>;
+  using G = XGeom<T, NX, PMAX, TL>;
   constexpr int NH = G::NH, E = G::E, TEAM = G::TEAM, ROWS = G::ROWS;
   constexpr int FB = PMAX + 1;
   __shared__ c2<T> lds[ROWS * G::REGION];
   __shared__ double red[2 * (G::WG / 64 + 1)];
+  // with the tiled layout lanes go in pieces of KTile, the rows' pieces in turn,
+  // so a wavefront's accesses cover R x KTile contiguous values
+  constexpr int KT = TEAM % KTile<T>::N == 0 ? KTile<T>::N : TEAM;
+  const bool tl = a.ts != KTile<T>::N;
   const int lane = threadIdx.x;
-  const int team = lane / TEAM;
-  const int t = lane - team * TEAM;
-  const int row = blockIdx.x * ROWS + team;
+  const int team = ROWS == 1 ? 0 : tl ? (lane / KT) % ROWS : lane / TEAM;
+  const int t = ROWS == 1 ? lane : tl ? lane / (KT * ROWS) * KT + lane % KT : lane % TEAM;
+  const int row0 = row_block<T>(a.ts) * ROWS;
+  const int row = row0 + team;
   const bool active = row < a.rows;
   const long long rrow = active ? row : 0;
+  const RowMap<T, NH, E> rm(t, a.ts, unsigned(team) * unsigned(a.rs));
   c2<T>* my = lds + team * G::REGION;
   const int F = FEK >= 0 ? PMAX + 1 : a.F;
   const int p = F - 1;
@@ -250,7 +318,7 @@ xpass_kernel(XArgs<T> a) {
 #pragma unroll
     for (int f = 0; f < FB; ++f)
       if (f < F)
-        row_load<T, NX, E>(u[f], xn[f], a.s_in + f * a.fs_spec + rrow * a.Sx,
+        row_load<T, NX, E>(u[f], xn[f], a.s_in + f * a.fs_spec + (long long)row0 * a.rs, rm,
                            a.s_in + f * a.fs_spec + a.nyo + rrow, active, t);
 #pragma unroll
     for (int f = 0; f < FB; ++f)
@@ -320,19 +388,19 @@ xpass_kernel(XArgs<T> a) {
       gcv[m] = mk<T>(gcx, gcy);
     }
     if (flags & X_WITH_C)
-      row_r2c<T, NX, E>(u[0], a.b_out + rrow * a.Sx, a.b_out + a.nyo + rrow, active, t, my, lt, tws);
-    row_r2c<T, NX, E>(gcv, a.b_out + 1 * a.fs_spec + rrow * a.Sx, a.b_out + 1 * a.fs_spec + a.nyo + rrow,
+      row_r2c<T, NX, E>(u[0], a.b_out + (long long)row0 * a.rs, rm, a.b_out + a.nyo + rrow, active, t, my, lt, tws);
+    row_r2c<T, NX, E>(gcv, a.b_out + 1 * a.fs_spec + (long long)row0 * a.rs, rm, a.b_out + 1 * a.fs_spec + a.nyo + rrow,
                       active, t, my, lt, tws);
 #pragma unroll
     for (int i = 0; i < PMAX; ++i)
       if (i < p)
-        row_r2c<T, NX, E>(u[1 + i], a.b_out + (2 + i) * a.fs_spec + rrow * a.Sx,
+        row_r2c<T, NX, E>(u[1 + i], a.b_out + (2 + i) * a.fs_spec + (long long)row0 * a.rs, rm,
                           a.b_out + (2 + i) * a.fs_spec + a.nyo + rrow, active, t, my, lt, tws);
   } else if (flags & X_FWD_RAW) {
 #pragma unroll
     for (int f = 0; f < FB; ++f)
       if (f < F)
-        row_r2c<T, NX, E>(u[f], a.b_out + f * a.fs_spec + rrow * a.Sx, a.b_out + f * a.fs_spec + a.nyo + rrow,
+        row_r2c<T, NX, E>(u[f], a.b_out + f * a.fs_spec + (long long)row0 * a.rs, rm, a.b_out + f * a.fs_spec + a.nyo + rrow,
                           active, t, my, lt, tws);
   }
 }
@@ -346,15 +414,16 @@ xpass_kernel(XArgs<T> a) {
 // area `ar`, which saves the registers of a second set of loads (one more
 // wavefront per SIMD on 256-point rows); otherwise both reads come from
 // global memory (measured faster where occupancy does not change).
-template <typename T, int NH, int E>
+template <typename T, int NH, int E, bool LIN>
 __device__ __forceinline__ void wave_c2r_pre(c2<T>* v, const c2<T>* __restrict__ src,
+                                             const RowMap<T, NH, E, LIN>& rm,
                                              const c2<T>* __restrict__ nyq, c2<T>* ar,
                                              int t, const LaneTwiddles<T, NH, E>& lt) {
   constexpr int TEAM = NH / E;
   constexpr bool STAGE = sizeof(T) == 4 && TEAM < 64;
   c2<T> X[E];
 #pragma unroll
-  for (int m = 0; m < E; ++m) X[m] = src[t + TEAM * m];
+  for (int m = 0; m < E; ++m) X[m] = src[rm.at(m)];
   if constexpr (STAGE) {
     const c2<T> xn = t == 0 ? *nyq : src[0];
 #pragma unroll
@@ -365,13 +434,81 @@ __device__ __forceinline__ void wave_c2r_pre(c2<T>* v, const c2<T>* __restrict__
 #pragma unroll
   for (int m = 0; m < E; ++m) {
     const int k = t + TEAM * m;
-    const c2<T> Y = conj<T>(STAGE ? ar[pad(NH - k)] : (k == 0 ? *nyq : src[(NH - k) & (NH - 1)]));
+    const c2<T> Y = conj<T>(STAGE ? ar[pad(NH - k)] : (k == 0 ? *nyq : src[rm.mirror(m)]));
     const c2<T> sm = add<T>(X[m], Y);
     const c2<T> d = cmulc<T>(sub<T>(X[m], Y), lt.w[m]);  // * exp(+2 pi i k / NX)
     v[m] = mk<T>(sm.x - d.y, sm.y + d.x);
   }
   if constexpr (STAGE) team_sync<true>();
 }
+
+// Output half of an R2C by one wavefront team: v holds the team's complex
+// transform, also in its LDS area `ar`; writes X[0..NH-1] and X[NH].
+template <typename T, int NH, int E, bool LIN>
+__device__ __forceinline__ void wave_r2c_post(const c2<T>* v, c2<T>* __restrict__ dst, const RowMap<T, NH, E, LIN>& rm,
+                                              c2<T>* __restrict__ nyq, const c2<T>* ar, int t,
+                                              const LaneTwiddles<T, NH, E>& lt) {
+  constexpr int TEAM = NH / E;
+#pragma unroll
+  for (int m = 0; m < E; ++m) {
+    const int k = t + TEAM * m;
+    const c2<T> Z = v[m];
+    const c2<T> Zc = conj<T>(ar[pad((NH - k) & (NH - 1))]);
+    const c2<T> sm = add<T>(Z, Zc);
+    const c2<T> d = sub<T>(Z, Zc);
+    const c2<T> B2 = mk<T>(d.y, -d.x);
+    const c2<T> WB = cmul<T>(B2, lt.w[m]);
+    dst[rm.at(m)] = mk<T>(T(0.5) * (sm.x + WB.x), T(0.5) * (sm.y + WB.y));
+    if (k == 0) *nyq = mk<T>(T(0.5) * (sm.x - B2.x), T(0.5) * (sm.y - B2.y));
+  }
+}
+
+// The real-transform halves of the wave-per-transform row passes, done by the
+// whole work-group between the transforms: each thread takes the pairs
+// (X_k, X_{NH-k}) of a fixed row and k for every field, so a pair costs one
+// complex multiplication and one twiddle, both values are read once, and with
+// the tiled layout a wavefront's accesses cover R x KTile contiguous values.  k = 0 stands for k = 0 with the Nyquist
+// value and for k = NH/2, its own mirror.  Against the transforms' own loads
+// (each value twice, and 32-byte pieces in the tiled layout): 1024 x 2048,
+// F = 5, FP32 row pass 40.5 us tiled, 27.8 row-major; see k_row.inc.
+template <typename T, int NX, int ROWS>
+struct PairMap {
+  static constexpr int NH = NX / 2;
+  static constexpr int KT = NH / 2 < KTile<T>::N ? NH / 2 : KTile<T>::N;
+  int k, r;
+  unsigned oa, ob;  // offsets of X_k and of X_{NH-k} (X_{NH/2} for k = 0)
+  c2<T> w;          // exp(-2 pi i k / NX)
+  __device__ __forceinline__ PairMap(int q, int rs, int ts, const double2* __restrict__ twx) {
+    const bool tl = ts != KTile<T>::N;
+    k = tl ? q / (KT * ROWS) * KT + q % KT : q % (NH / 2);
+    r = tl ? (q / KT) % ROWS : q / (NH / 2);
+    oa = unsigned(r) * unsigned(rs) + koff<T>(k, ts);
+    ob = unsigned(r) * unsigned(rs) + koff<T>(k ? NH - k : NH / 2, ts);
+    w = rnd<T>(twx[k]);
+  }
+  // input of the C2R's complex transform (see wave_c2r_pre) into the slot
+  __device__ __forceinline__ void c2r_pre(c2<T> A, c2<T> B, c2<T> nyq, c2<T>* slot) const {
+    const c2<T> Y = conj<T>(k ? B : nyq);
+    const c2<T> sm = add<T>(A, Y);
+    const c2<T> dw = cmulc<T>(sub<T>(A, Y), w);
+    slot[pad(k)] = mk<T>(sm.x - dw.y, sm.y + dw.x);
+    // the mirror, conj(sm) + i conj(dw); X_{NH/2} gives 2 conj(X)
+    const c2<T> mir = k ? mk<T>(sm.x + dw.y, dw.x - sm.y) : mk<T>(T(2) * B.x, T(-2) * B.y);
+    slot[pad(k ? NH - k : NH / 2)] = mir;
+  }
+  // the R2C's output values from the complex transform in the slot
+  __device__ __forceinline__ void r2c_post(const c2<T>* slot, c2<T>* __restrict__ dst, c2<T>* __restrict__ nyq) const {
+    const c2<T> Z = slot[pad(k)];
+    const c2<T> M = slot[pad(k ? NH - k : NH / 2)];
+    const c2<T> Zc = conj<T>(k ? M : Z);
+    const c2<T> sm = add<T>(Z, Zc);
+    const c2<T> d = sub<T>(Z, Zc);
+    const c2<T> WB = cmul<T>(mk<T>(d.y, -d.x), w);
+    dst[oa] = mk<T>(T(0.5) * (sm.x + WB.x), T(0.5) * (sm.y + WB.y));
+    dst[ob] = k ? mk<T>(T(0.5) * (sm.x - WB.x), T(0.5) * (WB.y - sm.y)) : conj<T>(M);
+    if (k == 0) *nyq = mk<T>(T(0.5) * (sm.x - d.y), T(0.5) * (sm.y + d.x));
+  }
+};
 
 // ---------------------------------------------------------------------------
 // Row pass, one wavefront per transform.  The work-group owns ROWS rows and
@@ -390,7 +527,8 @@ __device__ __forceinline__ void wave_c2r_pre(c2<T>* v, const c2<T>* __restrict__
 // SM selects the form for grids with few rows: as many rows as one wavefront
 // has room for (one where a row's F transforms fill it), which spreads a
 // small grid over more compute units than 1024-point work-groups would.
-template <typename T, int NX, int PMAX, bool SM = false>
+// TL selects the form for the tiled layout where there is one (TWO).
+template <typename T, int NX, int PMAX, bool SM = false, bool TL = false>
 struct RGeom {
   static constexpr int NH = NX / 2;
   static constexpr int E = NH >= 512 ? (NH / 64 < 16 ? NH / 64 : 16) : (NH < 8 ? NH : 8);
@@ -408,7 +546,7 @@ struct RGeom {
   // register form at 2048 points; the adjoint row pass keeps this one.)
   static constexpr int SM_ROWS = UPW > PMAX ? 1 << ilog2(UPW / (PMAX + 1)) : 1;
   static constexpr int BASE_ROWS = SM ? SM_ROWS : (NX >= 1024 ? 1 : 1024 / NX);
-  static constexpr int MULT_WANT = NX == 2048 ? PF_ROW_MULT_2048 : NX == 1024 ? PF_ROW_ROWS_LONG : PF_ROW_MULT_SHORT;
+  static constexpr int MULT_WANT = NX == 2048 ? PF_ROW_MULT_2048 : NX == 1024 ? (TL ? 2 : PF_ROW_ROWS_LONG) : PF_ROW_MULT_SHORT;
   static constexpr bool MULTI = !SM && NX <= 2048 && sizeof(T) == 4 && PF_ROW_NW > 0 && MULT_WANT > 1 &&
                                 PF_ROW_NW * MULT_WANT <= 16 &&
                                 MULT_WANT * BASE_ROWS * ROW_BYTES <= 160 * 1024;
@@ -418,6 +556,16 @@ struct RGeom {
                                : (PF_ROW_NW > 0 ? PF_ROW_NW * MULT : PMAX + 1);
   static constexpr int WG = 64 * NW;
   static constexpr long LDS_BYTES = long(ROWS) * ROW_BYTES;
+  // pairs (kx, NH - kx) per thread (PairMap).  Not on row-major 1024-point
+  // rows: their work-groups fill the chip once, and the two more barriers cost
+  // more than the arithmetic saved (1024^2, F = 5, FP32 13.8 -> 16.0 us; 512 x
+  // 1024 10.5 -> 10.3).  Tiled 1024-point float rows go by two (1024 x 2048:
+  // 27.7 us, by four 32.5; without the pairs 40.5; row-major 27.7).
+  // Row-major 512-point double rows: 512 x 64 x 64 step, F = 5, 130 -> 133 us.
+  static constexpr int PAIRS = ROWS * (NH / 2) / WG;
+  static constexpr bool TWO = NX == 1024 || (NX == 512 && sizeof(T) == 8);  // a form for each layout
+  static constexpr bool LIN = TWO && !TL && !SM;  // only launched on the row-major layout
+  static constexpr bool COOP = !SM && ROWS * (NH / 2) == PAIRS * WG && PAIRS >= 1 && !LIN;
   static constexpr bool FITS = WAVE_OK && LDS_BYTES <= (MULTI ? 160 : 96) * 1024;
   // register budget: enough waves per SIMD for four work-groups per CU
   static constexpr int MIN_WAVES = (sizeof(T) == 4 && PMAX <= 4) ? PF_ROW_MIN_WAVES : 1;
@@ -427,11 +575,11 @@ struct RGeom {
 // steady-state step gets a lean instantiation); FX = -1 reads them from the
 // arguments.  FEK >= 0
 // fixes the free-energy kind and requires p = PMAX.
-template <typename T, int NX, int PMAX, int FX, int FEK = -1, bool SM = false>
-__global__ void __attribute__((amdgpu_flat_work_group_size(1, RGeom<T, NX, PMAX, SM>::WG),
-                               amdgpu_waves_per_eu(FX >= 0 ? RGeom<T, NX, PMAX, SM>::MIN_WAVES : 1)))
+template <typename T, int NX, int PMAX, int FX, int FEK = -1, bool SM = false, bool TL = false>
+__global__ void __attribute__((amdgpu_flat_work_group_size(1, RGeom<T, NX, PMAX, SM, TL>::WG),
+                               amdgpu_waves_per_eu(FX >= 0 ? RGeom<T, NX, PMAX, SM, TL>::MIN_WAVES : 1)))
 rowpass_kernel(XArgs<T> a) {
-  using G = RGeom<T, NX, PMAX, SM>;
+  using G = RGeom<T, NX, PMAX, SM, TL>;
   constexpr int NH = G::NH, E = G::E, TEAM = G::TEAM, UPW = G::UPW, ROWS = G::ROWS;
   constexpr int NW = G::NW, SL = G::SLOTS, WG = G::WG, SC = G::SLOT_C;
   static_assert(G::FITS, "row pass v2 does not fit this size");
@@ -444,7 +592,8 @@ rowpass_kernel(XArgs<T> a) {
   const int lane = tid & 63;
   const int unit = lane / TEAM;
   const int t = lane - unit * TEAM;
-  const int row0 = blockIdx.x * ROWS;
+  const int row0 = row_block<T>(a.ts) * ROWS;
+  const RowMap<T, NH, E, G::LIN> rm(t, a.ts, 0);
   const int F = FEK >= 0 ? PMAX + 1 : a.F;  // the fixed-kind instantiations have p = PMAX
   const int p = F - 1;
   // the store flag stays a run-time choice even in the fixed instantiations,
@@ -453,7 +602,7 @@ rowpass_kernel(XArgs<T> a) {
   Twiddles<T, NH, E> tws;
   tws.load(t, a.twx, 2);
   LaneTwiddles<T, NH, E> lt;  // exp(-2 pi i k / NX), k = t + TEAM m
-  lt.load(t, a.twx);
+  if constexpr (!G::COOP) lt.load(t, a.twx);
 
   // phase 1: real rows into the row buffer
   if (flags & X_LOAD_REAL) {
@@ -473,6 +622,43 @@ rowpass_kernel(XArgs<T> a) {
         ar[pad(x2)] = src[x2];
       }
     }
+  } else if constexpr (G::COOP) {
+#pragma unroll
+    for (int i = 0; i < G::PAIRS; ++i) {
+      const PairMap<T, NX, ROWS> pm(tid + i * WG, a.rs, a.ts, a.twx);
+      if (row0 + pm.r < a.rows) {
+        const c2<T>* src = a.s_in + (long long)row0 * a.rs;
+        c2<T> A[PMAX + 1], B[PMAX + 1], N[PMAX + 1];
+#pragma unroll
+        for (int f = 0; f <= PMAX; ++f)
+          if (f < F) {
+            A[f] = src[f * a.fs_spec + pm.oa];
+            B[f] = src[f * a.fs_spec + pm.ob];
+            N[f] = pm.k == 0 ? a.s_in[f * a.fs_spec + a.nyo + row0 + pm.r] : mk<T>(T(0), T(0));
+          }
+#pragma unroll
+        for (int f = 0; f <= PMAX; ++f)
+          if (f < F) pm.c2r_pre(A[f], B[f], N[f], rb + (pm.r * SL + (f == 0 ? 0 : f + 1)) * SC);
+      }
+    }
+    __syncthreads();
+    const int njobs = ROWS * F;
+    for (int base = wave * UPW; base < njobs; base += NW * UPW) {
+      const int j = base + unit;
+      const int f = j / ROWS;
+      const int r = j - f * ROWS;
+      if (j < njobs && row0 + r < a.rows) {
+        c2<T>* ar = rb + (r * SL + (f == 0 ? 0 : f + 1)) * SC;
+        c2<T> v[E];
+#pragma unroll
+        for (int m = 0; m < E; ++m) v[m] = ar[pad(t + TEAM * m)];
+        team_sync<true>();
+        team_fft<T, NH, E, true, 1, true>(v, t, ar, tws);
+        team_sync<true>();
+#pragma unroll
+        for (int m = 0; m < E; ++m) ar[pad(t + TEAM * m)] = v[m];
+      }
+    }
   } else {
     const int njobs = ROWS * F;
     for (int base = wave * UPW; base < njobs; base += NW * UPW) {
@@ -480,11 +666,11 @@ rowpass_kernel(XArgs<T> a) {
       const int r = j / F;
       const int f = j - r * F;
       if (j < njobs && row0 + r < a.rows) {
-        const c2<T>* src = a.s_in + f * a.fs_spec + (long long)(row0 + r) * a.Sx;
+        const c2<T>* src = a.s_in + f * a.fs_spec + (long long)(row0 + r) * a.rs;
         const c2<T>* nyq = a.s_in + f * a.fs_spec + a.nyo + (row0 + r);
         c2<T>* ar = rb + (r * SL + (f == 0 ? 0 : f + 1)) * SC;
         c2<T> v[E];
-        wave_c2r_pre<T, NH, E>(v, src, nyq, ar, t, lt);
+        wave_c2r_pre<T, NH, E, G::LIN>(v, src, rm, nyq, ar, t, lt);
         team_fft<T, NH, E, true, 1, true>(v, t, ar, tws);
         team_sync<true>();
 #pragma unroll
@@ -569,20 +755,25 @@ rowpass_kernel(XArgs<T> a) {
         team_sync<true>();
 #pragma unroll
         for (int m = 0; m < E; ++m) ar[pad(t + TEAM * m)] = v[m];
-        team_sync<true>();
-        c2<T>* dst = a.b_out + o * a.fs_spec + (long long)(row0 + r) * a.Sx;
-        c2<T>* dstn = a.b_out + o * a.fs_spec + a.nyo + (row0 + r);
+        if constexpr (!G::COOP) {
+          team_sync<true>();
+          wave_r2c_post<T, NH, E, G::LIN>(v, a.b_out + o * a.fs_spec + (long long)(row0 + r) * a.rs, rm,
+                                  a.b_out + o * a.fs_spec + a.nyo + (row0 + r), ar, t, lt);
+        }
+      }
+    }
+    if constexpr (G::COOP) {
+      __syncthreads();
 #pragma unroll
-        for (int m = 0; m < E; ++m) {
-          const int k = t + TEAM * m;
-          const c2<T> Z = v[m];
-          const c2<T> Zc = conj<T>(ar[pad((NH - k) & (NH - 1))]);
-          const c2<T> sm = add<T>(Z, Zc);
-          const c2<T> d = sub<T>(Z, Zc);
-          const c2<T> B2 = mk<T>(d.y, -d.x);
-          const c2<T> WB = cmul<T>(B2, lt.w[m]);
-          dst[k] = mk<T>(T(0.5) * (sm.x + WB.x), T(0.5) * (sm.y + WB.y));
-          if (k == 0) *dstn = mk<T>(T(0.5) * (sm.x - B2.x), T(0.5) * (sm.y - B2.y));
+      for (int i = 0; i < G::PAIRS; ++i) {
+        const PairMap<T, NX, ROWS> pm(tid + i * WG, a.rs, a.ts, a.twx);
+        if (row0 + pm.r < a.rows) {
+#pragma unroll
+          for (int o = 0; o < PMAX + 2; ++o)
+            if (o >= skip && o < skip + nout)
+              pm.r2c_post(rb + (pm.r * SL + (deriv ? o : (o == 0 ? 0 : o + 1))) * SC,
+                          a.b_out + o * a.fs_spec + (long long)row0 * a.rs,
+                          a.b_out + o * a.fs_spec + a.nyo + (row0 + pm.r));
         }
       }
     }
@@ -620,7 +811,7 @@ struct AdjArgs {
   double* partials;
   long long fs_real, fs_spec;
   long long nyo;  // offset of the Nyquist values within an x-spectrum field
-  int rows, Sx, F, do_fwd;
+  int rows, rs, ts, F, do_fwd;
   int first;  // first adjoint step of a segment: start the partial sums
   FeParams<T> fe;
   T dtM, dtL;
@@ -656,9 +847,12 @@ adj_row_kernel(AdjArgs<T> a) {
   const int lane = threadIdx.x;
   const int team = lane / TEAM;
   const int t = lane - team * TEAM;
-  const int row = blockIdx.x * ROWS + team;
+  const int row0 = row_block<T>(a.ts) * ROWS;
+  const int row = row0 + team;
   const bool active = row < a.rows;
   const long long rrow = active ? row : 0;
+  const RowMap<T, G::NH, E> rm(t, a.ts, unsigned(team) * unsigned(a.rs));
+  const long long rs0 = (long long)row0 * a.rs;
   c2<T>* my = lds + team * G::REGION;
   constexpr int F = PMAX + 1;
   const int p = F - 1;
@@ -669,13 +863,13 @@ adj_row_kernel(AdjArgs<T> a) {
 
   // w[0] = e_c, w[1..p] = e_i, bc = b_c; w is overwritten by lambda^n
   c2<T> w[FB][E], bc[E], xn[FB + 1];
-  row_load<T, NX, E>(w[0], xn[0], a.s_in + rrow * a.Sx, a.s_in + a.nyo + rrow, active, t);
-  row_load<T, NX, E>(bc, xn[FB], a.s_in + a.fs_spec + rrow * a.Sx, a.s_in + a.fs_spec + a.nyo + rrow,
+  row_load<T, NX, E>(w[0], xn[0], a.s_in + rs0, rm, a.s_in + a.nyo + rrow, active, t);
+  row_load<T, NX, E>(bc, xn[FB], a.s_in + a.fs_spec + rs0, rm, a.s_in + a.fs_spec + a.nyo + rrow,
                      active, t);
 #pragma unroll
   for (int i = 0; i < PMAX; ++i)
     if (i < p)
-      row_load<T, NX, E>(w[1 + i], xn[1 + i], a.s_in + (2 + i) * a.fs_spec + rrow * a.Sx,
+      row_load<T, NX, E>(w[1 + i], xn[1 + i], a.s_in + (2 + i) * a.fs_spec + rs0, rm,
                          a.s_in + (2 + i) * a.fs_spec + a.nyo + rrow, active, t);
   row_c2r<T, NX, E>(w[0], xn[0], t, my, lt, tws);
   row_c2r<T, NX, E>(bc, xn[FB], t, my, lt, tws);
@@ -746,7 +940,7 @@ adj_row_kernel(AdjArgs<T> a) {
 #pragma unroll
     for (int f = 0; f < FB; ++f)
       if (f < F)
-        row_r2c<T, NX, E>(w[f], a.b_out + f * a.fs_spec + rrow * a.Sx, a.b_out + f * a.fs_spec + a.nyo + rrow,
+        row_r2c<T, NX, E>(w[f], a.b_out + f * a.fs_spec + rs0, rm, a.b_out + f * a.fs_spec + a.nyo + rrow,
                           active, t, my, lt, tws);
   }
 }
@@ -755,10 +949,10 @@ adj_row_kernel(AdjArgs<T> a) {
 // structure and geometry, SM included).  Slots: 0 = e_c, 1 = b_c, 2 + i =
 // e_i; the pointwise phase overwrites slots 0 and 2 + i with lambda^n for the
 // forward transforms of phase 3.  The order-parameter count is PMAX.
-template <typename T, int NX, int PMAX, bool SM>
-__global__ void __attribute__((amdgpu_flat_work_group_size(1, RGeom<T, NX, PMAX, SM>::WG)))
+template <typename T, int NX, int PMAX, bool SM, bool TL>
+__global__ void __attribute__((amdgpu_flat_work_group_size(1, RGeom<T, NX, PMAX, SM, TL>::WG)))
 adjrow_kernel(AdjArgs<T> a) {
-  using G = RGeom<T, NX, PMAX, SM>;
+  using G = RGeom<T, NX, PMAX, SM, TL>;
   constexpr int NH = G::NH, E = G::E, TEAM = G::TEAM, UPW = G::UPW, ROWS = G::ROWS;
   constexpr int NW = G::NW, SL = G::SLOTS, WG = G::WG, SC = G::SLOT_C;
   static_assert(G::FITS, "adjoint row pass v2 does not fit this size");
@@ -769,28 +963,53 @@ adjrow_kernel(AdjArgs<T> a) {
   const int lane = tid & 63;
   const int unit = lane / TEAM;
   const int t = lane - unit * TEAM;
-  const int row0 = blockIdx.x * ROWS;
+  const int row0 = row_block<T>(a.ts) * ROWS;
+  const RowMap<T, NH, E, G::LIN> rm(t, a.ts, 0);
   constexpr int F = PMAX + 1;
   const int p = F - 1;
   Twiddles<T, NH, E> tws;
   tws.load(t, a.twx, 2);
   LaneTwiddles<T, NH, E> lt;
-  lt.load(t, a.twx);
+  if constexpr (!G::COOP) lt.load(t, a.twx);
 
   // phase 1: C2R of the F + 1 adjoint x-spectra into slots 0..F
+  constexpr int NIN = F + 1;
+  if constexpr (G::COOP) {
+#pragma unroll
+    for (int i = 0; i < G::PAIRS; ++i) {
+      const PairMap<T, NX, ROWS> pm(tid + i * WG, a.rs, a.ts, a.twx);
+      if (row0 + pm.r < a.rows) {
+        const c2<T>* src = a.s_in + (long long)row0 * a.rs;
+        c2<T> A[NIN], B[NIN], N[NIN];
+#pragma unroll
+        for (int f = 0; f < NIN; ++f) {
+          A[f] = src[f * a.fs_spec + pm.oa];
+          B[f] = src[f * a.fs_spec + pm.ob];
+          N[f] = pm.k == 0 ? a.s_in[f * a.fs_spec + a.nyo + row0 + pm.r] : mk<T>(T(0), T(0));
+        }
+#pragma unroll
+        for (int f = 0; f < NIN; ++f) pm.c2r_pre(A[f], B[f], N[f], rb + (pm.r * SL + f) * SC);
+      }
+    }
+    __syncthreads();
+  }
   {
-    const int nin = F + 1;
-    const int njobs = ROWS * nin;
+    const int njobs = ROWS * NIN;
     for (int base = wave * UPW; base < njobs; base += NW * UPW) {
       const int j = base + unit;
-      const int r = j / nin;
-      const int sl = j - r * nin;
+      const int sl = j / ROWS;
+      const int r = j - sl * ROWS;
       if (j < njobs && row0 + r < a.rows) {
-        const c2<T>* src = a.s_in + sl * a.fs_spec + (long long)(row0 + r) * a.Sx;
-        const c2<T>* nyq = a.s_in + sl * a.fs_spec + a.nyo + (row0 + r);
         c2<T>* ar = rb + (r * SL + sl) * SC;
         c2<T> v[E];
-        wave_c2r_pre<T, NH, E>(v, src, nyq, ar, t, lt);
+        if constexpr (G::COOP) {
+#pragma unroll
+          for (int m = 0; m < E; ++m) v[m] = ar[pad(t + TEAM * m)];
+          team_sync<true>();
+        } else {
+          wave_c2r_pre<T, NH, E, G::LIN>(v, a.s_in + sl * a.fs_spec + (long long)(row0 + r) * a.rs, rm,
+                                 a.s_in + sl * a.fs_spec + a.nyo + (row0 + r), ar, t, lt);
+        }
         team_fft<T, NH, E, true, 1, true>(v, t, ar, tws);
         team_sync<true>();
 #pragma unroll
@@ -881,8 +1100,8 @@ adjrow_kernel(AdjArgs<T> a) {
     const int njobs = ROWS * F;
     for (int base = wave * UPW; base < njobs; base += NW * UPW) {
       const int j = base + unit;
-      const int r = j / F;
-      const int f = j - r * F;
+      const int f = j / ROWS;
+      const int r = j - f * ROWS;
       if (j < njobs && row0 + r < a.rows) {
         c2<T>* ar = rb + (r * SL + (f == 0 ? 0 : f + 1)) * SC;
         c2<T> v[E];
@@ -893,20 +1112,23 @@ adjrow_kernel(AdjArgs<T> a) {
         team_sync<true>();
 #pragma unroll
         for (int m = 0; m < E; ++m) ar[pad(t + TEAM * m)] = v[m];
-        team_sync<true>();
-        c2<T>* dst = a.b_out + f * a.fs_spec + (long long)(row0 + r) * a.Sx;
-        c2<T>* dstn = a.b_out + f * a.fs_spec + a.nyo + (row0 + r);
+        if constexpr (!G::COOP) {
+          team_sync<true>();
+          wave_r2c_post<T, NH, E, G::LIN>(v, a.b_out + f * a.fs_spec + (long long)(row0 + r) * a.rs, rm,
+                                  a.b_out + f * a.fs_spec + a.nyo + (row0 + r), ar, t, lt);
+        }
+      }
+    }
+    if constexpr (G::COOP) {
+      __syncthreads();
 #pragma unroll
-        for (int m = 0; m < E; ++m) {
-          const int k = t + TEAM * m;
-          const c2<T> Z = v[m];
-          const c2<T> Zc = conj<T>(ar[pad((NH - k) & (NH - 1))]);
-          const c2<T> sm = add<T>(Z, Zc);
-          const c2<T> d = sub<T>(Z, Zc);
-          const c2<T> B2 = mk<T>(d.y, -d.x);
-          const c2<T> WB = cmul<T>(B2, lt.w[m]);
-          dst[k] = mk<T>(T(0.5) * (sm.x + WB.x), T(0.5) * (sm.y + WB.y));
-          if (k == 0) *dstn = mk<T>(T(0.5) * (sm.x - B2.x), T(0.5) * (sm.y - B2.y));
+      for (int i = 0; i < G::PAIRS; ++i) {
+        const PairMap<T, NX, ROWS> pm(tid + i * WG, a.rs, a.ts, a.twx);
+        if (row0 + pm.r < a.rows) {
+#pragma unroll
+          for (int f = 0; f < F; ++f)
+            pm.r2c_post(rb + (pm.r * SL + (f == 0 ? 0 : f + 1)) * SC, a.b_out + f * a.fs_spec + (long long)row0 * a.rs,
+                        a.b_out + f * a.fs_spec + a.nyo + (row0 + pm.r));
         }
       }
     }
@@ -932,6 +1154,7 @@ struct ColArgs {
   double* partials;
   long long fs_src, fs_dst;  // field strides (complex elements)
   long long ls;              // stride between consecutive transform elements
+  int ts;                    // tile stride of the x-spectra (KTile: row-major)
   long long os;              // stride between outer planes
   long long nyo;             // offset of the Nyquist values within a field
   long long nls, nos;        // Nyquist values: element stride, outer-row stride
@@ -955,7 +1178,7 @@ template <typename T, int N>
 struct ColGeom {
   static constexpr int E = N <= 8 ? N : ((N >= 512 && sizeof(T) == 4) ? PF_COL_E_LONG_F32 : 8);
   static constexpr int TEAM = N / E;
-  static constexpr int CB = N >= 512 ? (sizeof(T) == 8 ? PF_COL_CB_LONG_F64 : PF_COL_CB_LONG_F32)
+  static constexpr int CB = N >= PF_COL_X_FROM ? (sizeof(T) == 8 ? PF_COL_CX_F64 : PF_COL_CX_F32) : N >= 512 ? (sizeof(T) == 8 ? PF_COL_CB_LONG_F64 : PF_COL_CB_LONG_F32)
                                     : (sizeof(T) == 8 ? 8 : 16);
   static constexpr int C0 = (CB * TEAM < 64) ? 64 / TEAM : CB;
   static constexpr int WGMAX = (sizeof(T) == 4 && N >= 4096) ? PF_COL_WG_MAX_LONG : 512;
@@ -1070,8 +1293,10 @@ col_kernel(ColArgs<T> a, int tiles, int nouter, int ngroups, int nslots, int nqb
   // the scalar unit.  The offset is below 2^32 for every supported shape
   // (at most C + TEAM ls complex values).
   const long long ls = nyqi ? a.nls : a.ls;
-  const long long wg0 = nyqi ? a.nyo + (long long)o * a.nos : (long long)o * a.os + (long long)tile * C;
-  const unsigned lbo = (unsigned(cc) * unsigned(nyqi ? a.nos : 1) + unsigned(t) * unsigned(ls)) *
+  const long long wg0 = nyqi ? a.nyo + (long long)o * a.nos : (long long)o * a.os + (long long)koff<T>(tile * C, a.ts);
+  // (C divides KTile or the other way round, so a tile's columns add up)
+  const unsigned lco = C > KTile<T>::N ? koff<T>(cc, a.ts) : unsigned(cc);
+  const unsigned lbo = ((nyqi ? unsigned(cc) * unsigned(a.nos) : lco) + unsigned(t) * unsigned(ls)) *
                        unsigned(sizeof(c2<T>));
   auto load = [&](const c2<T>* src, c2<T>* v) {
 #pragma unroll
@@ -1111,6 +1336,34 @@ col_kernel(ColArgs<T> a, int tiles, int nouter, int ngroups, int nslots, int nqb
     store(a.dst + (g + a.f0) * a.fs_dst, v);
   } else if constexpr (MODE == COL_UPDATE || MODE == COL_UPDATE_FIRST) {
     if (g == 0) {
+      // the held k = 0 mode: P times the double-precision mean of c.  On the
+      // first step of a call the work item that holds it (tile 0, outer row
+      // 0) adds up the row pass's per-group sums of c in a fixed order and
+      // keeps the mean for the later steps; the row pass has completed (a
+      // kernel boundary), so no fence is needed.  (Before the transforms: after
+      // them the eight loads in flight cost the whole kernel registers, 2048 x
+      // 1024, F = 5, FP32 one-step call 72 -> 80 us.)
+      double cmean = 0.0;
+      if constexpr (MODE == COL_UPDATE_FIRST) {
+        if (tile == 0 && o == 0) {  // work-group uniform
+          double acc[1] = {0.0};
+          for (int r0 = threadIdx.x; r0 < a.nrec; r0 += 8 * G::WG) {  // eight loads in flight
+            double v8[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v8[u] = a.partials[2 * (long long)min(r0 + u * G::WG, a.nrec - 1) + 1];
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+              if (r0 + u * G::WG < a.nrec) acc[0] += v8[u];
+          }
+          block_sum<1>(acc, red);
+          if (threadIdx.x == 0) {
+            cmean = acc[0] * a.invPd;
+            *a.mean_c = cmean;
+          }
+        }
+      } else {
+        if (col == 0 && o == 0 && t == 0) cmean = *a.mean_c;
+      }
       // c (carried spectrum, Algorithm 1): c^ <- (c^ - dt M k2 g^) / (1 + dt M kappa_c k2^2);
       // the inverse transform gets c^ / P with the k = 0 mode held in double.
       // Both column arrays are loaded up front so their latencies overlap.
@@ -1123,25 +1376,6 @@ col_kernel(ColArgs<T> a, int tiles, int nouter, int ngroups, int nslots, int nqb
       }
       par = team_fft<T, N, E, false, C>(gg, t, my, tws, my2, par);
       if constexpr (MODE == COL_UPDATE_FIRST) par = team_fft<T, N, E, false, C>(v, t, my, tws, my2, par);
-      // the held k = 0 mode: P times the double-precision mean of c.  On the
-      // first step of a call the work item that holds it (tile 0, outer row
-      // 0) adds up the row pass's per-group sums of c in a fixed order and
-      // keeps the mean for the later steps; the row pass has completed (a
-      // kernel boundary), so no fence is needed.
-      double cmean = 0.0;
-      if constexpr (MODE == COL_UPDATE_FIRST) {
-        if (tile == 0 && o == 0) {  // work-group uniform
-          double acc[1] = {0.0};
-          for (int r = threadIdx.x; r < a.nrec; r += blockDim.x) acc[0] += a.partials[2 * (long long)r + 1];
-          block_sum<1>(acc, red);
-          if (threadIdx.x == 0) {
-            cmean = acc[0] * a.invPd;
-            *a.mean_c = cmean;
-          }
-        }
-      } else {
-        if (col == 0 && o == 0 && t == 0) cmean = *a.mean_c;
-      }
 #pragma unroll
       for (int m = 0; m < E; ++m) {
         const T k2 = kc + kaxis(m);

@@ -17,6 +17,28 @@
 
 using namespace pf;
 
+// 2D grids with the tiled x-spectrum layout (pf_kernels.h).  A compute unit
+// fetches whole 128-byte lines, of which a column work-group of two or four
+// columns used 16 or 32 bytes in the row-major layout; the row passes pay for
+// the tiles where their work-groups are few.  FS step, F = 5, row-major / tiled:
+//   FP32 4096^2 649 / 549 us, 2048^2 125 / 103, 1024 x 2048 60.8 / 51.1, 512 x
+//   2048 38.2 / 33.8, 512 x 1024 27.7 / 26.4, 64 x 1024 14.4 / 12.1; but 1024^2
+//   31.6 / 33.1, 512^2 16.9 / 18.5
+//   FP64 4096^2 1420 / 1198, 2048^2 262 / 244, 1024^2 53.7 / 52.9, 2048 x 512
+//   59.1 / 55.0; but 1024 x 512 31.2 / 32.8, and 512^2 25.1 / 24 or 31 by the
+//   place of the buffers in memory
+// With more than four order parameters (p = 8) the line lies higher: FP64 1024^2
+// 99 / 104, FP32 1024 x 2048 95 / 96.  One or more lines of padding per tile: no
+// faster (2048^2 FP64 244 / 252, 4096^2 FP32 549 / 552, 1024^2 FP64 52.9 / 54).
+static bool tiled_layout(int ndim, int nx, int ny, int p, bool f32) {
+  if (ndim != 2) return false;
+  const bool few = p <= 4;
+  if (ny >= 2048) return few || !f32 || nx != 1024;
+  if (f32) return ny >= 1024 && nx <= 512;
+  if (ny >= 1024) return few || nx != 1024;
+  return ny >= 512 && few && nx >= 2048;
+}
+
 namespace {
 
 thread_local std::string g_err;
@@ -45,7 +67,8 @@ struct ProfRec {
 
 struct pf_handle {
   pf_config cfg;
-  int nd, nx, ny, nz, F, p, nxh, Sx, rows;
+  int nd, nx, ny, nz, F, p, nxh, rows;
+  int rs, ts;     // row and tile stride of the x-spectra
   long long nyo;  // offset of the Nyquist values within an x-spectrum field
   long long P;
   size_t es;  // bytes per real element
@@ -192,7 +215,8 @@ XArgs<T> xargs(const pf_handle* h) {
   a.fs_real = h->P;
   a.fs_spec = (long long)h->spec_field;
   a.rows = h->rows;
-  a.Sx = h->Sx;
+  a.rs = h->rs;
+  a.ts = h->ts;
   a.nyo = h->nyo;
   a.F = h->F;
   a.fe = fe_params<T>(h);
@@ -221,6 +245,7 @@ ColArgs<T> cargs(const pf_handle* h, double dt) {
   a.ncols = h->nx / 2;
   a.nyq = h->nx / 2;
   a.nyo = h->nyo;
+  a.ts = h->ts;
   a.F = h->F;
   a.dtM = T(dt * h->M);
   a.dtMkc = T(dt * h->M * h->kc);
@@ -234,11 +259,11 @@ ColArgs<T> cargs(const pf_handle* h, double dt) {
 // Strided-axis pass.  axis 1 = y, axis 2 = z.
 template <typename T>
 pf_status col(pf_handle* h, ColArgs<T>& a, int axis, int* nblk) {
-  const long long plane = (long long)h->ny * h->Sx;
+  const long long plane = (long long)h->ny * h->rs;  // (3D: row-major)
   int n, nouter;
   if (axis == 1) {
     n = h->ny;
-    a.ls = h->Sx;
+    a.ls = h->rs;
     a.os = plane;
     a.nls = 1;  // Nyquist values: [z][y], contiguous along y
     a.nos = h->ny;
@@ -249,7 +274,7 @@ pf_status col(pf_handle* h, ColArgs<T>& a, int axis, int* nblk) {
   } else {
     n = h->nz;
     a.ls = plane;
-    a.os = h->Sx;
+    a.os = h->rs;
     a.nls = h->ny;
     a.nos = 1;
     nouter = h->ny;
@@ -549,7 +574,8 @@ pf_status adjoint_run(pf_handle* h, double dt, long long k, const T* u0, T* lam,
     r.fs_real = h->P;
     r.fs_spec = (long long)h->spec_field;
     r.rows = h->rows;
-    r.Sx = h->Sx;
+    r.rs = h->rs;
+    r.ts = h->ts;
     r.nyo = h->nyo;
     r.F = h->F;
     r.do_fwd = n > 0 ? 1 : 0;
@@ -659,16 +685,24 @@ pf_status pf_create(const pf_config* cfg, pf_handle** out) {
   h->es = c.prec == PF_F32 ? 4 : 8;
   const int align_c = c.prec == PF_F32 ? 16 : 8;  // complex values per 128 bytes
   // x-spectrum rows hold kx = 0 .. Nx/2 - 1; the Nyquist values follow the
-  // rows as one array per field.  In 2D each row carries one more 128-byte
-  // segment: the column pass strides along y by the row length, and a
-  // power-of-two row stride made its concurrent accesses collide (measured:
-  // 1024^2 FP32 column pass 17.7 -> 16.5 us, 4096^2 FP64 1.60 -> 0.95 ms),
-  // except on float rows of 4096 points, where the unpadded 16 KiB stride
-  // measured faster (0.43 against 0.47 ms).  3D rows (and planes) are not
-  // padded: no gain was measured there.
-  h->Sx = (h->nx / 2 + align_c - 1) / align_c * align_c;
-  if (c.ndim == 2 && !(c.prec == PF_F32 && h->nx == 4096)) h->Sx += align_c;
+  // rows as one array per field, in both layouts.  Row-major 2D rows carry
+  // one more 128-byte segment: the column pass strides along y by the row
+  // length, and a power-of-two row stride made its concurrent accesses
+  // collide (1024^2 FP32 column pass 17.7 -> 16.5 us), except float rows of
+  // 4096 points, where the unpadded 16 KiB stride measured faster.  3D rows
+  // (and planes) are not padded: no gain was measured there.
+  const int ktile = c.prec == PF_F32 ? KTile<float>::N : KTile<double>::N;
   h->rows = h->ny * h->nz;
+  if (tiled_layout(c.ndim, h->nx, h->ny, c.p, c.prec == PF_F32)) {
+    h->rs = ktile;
+    h->ts = ktile * h->ny;
+    h->nyo = (long long)(h->nx / 2) * h->ny;
+  } else {
+    h->rs = (h->nx / 2 + align_c - 1) / align_c * align_c;
+    if (c.ndim == 2 && !(c.prec == PF_F32 && h->nx == 4096)) h->rs += align_c;
+    h->ts = ktile;
+    h->nyo = (long long)h->rows * h->rs;
+  }
   h->P = (long long)h->nx * h->ny * h->nz;
   h->M = c.M;
   h->kc = c.kappa_c;
@@ -683,7 +717,6 @@ pf_status pf_create(const pf_config* cfg, pf_handle** out) {
   }
   // workspace layout
   const size_t cbytes = 2 * h->es;
-  h->nyo = (long long)h->rows * h->Sx;
   h->spec_field = size_t(h->nyo) + (size_t(h->rows) + align_c - 1) / align_c * align_c;
   size_t off = 0;
   h->off_B = off;
