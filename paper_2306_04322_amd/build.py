@@ -23,7 +23,7 @@ LIB = os.path.join(PKG, "libpfspec.so")
 # (the slowest first: they set the build time)
 ROW_F32 = ["k_row_f32_p78.hip", "k_row_f32_p56.hip", "k_row_f32_p34.hip", "k_row_f32.hip"]
 ROW_F64 = [n.replace("f32", "f64") for n in ROW_F32]
-SOURCES = ROW_F32 + ROW_F64 + ["k_adj_f32.hip", "k_adj_f64.hip", "k_fd.hip", "k_col_f32.hip",
+SOURCES = ROW_F32 + ROW_F64 + ["k_col2_f32.hip", "k_col2_f64.hip", "k_adj_f32.hip", "k_adj_f64.hip", "k_fd.hip", "k_col_f32.hip",
                                "k_col_f64.hip", "pfspec.hip", "k_reduce.hip"]
 
 ARCH = "gfx950"

@@ -289,4 +289,105 @@ __device__ __forceinline__ int team_fft(c2<T>* v, int t, c2<T>* lds, const Twidd
   return par + Twiddles<T, N, E>::P - 1;
 }
 
+// Transforms along the slow axis of an L x W array held by one team: element i
+// = l W + o of the N = L W elements, lane t holding i = t + (N/E) m as above.
+// Combining NS points along l for every o is the length-N pass after NS W
+// points with the twiddles of length L, so the passes are the 1D ones started
+// at NS W = W.  Twiddles: one pass of radix first_radix<L, E>, then radix E.
+template <typename T, int L, int W, int E>
+struct AxisTwiddles {
+  static constexpr int P = num_passes<L, E>();
+  static constexpr int NT = (P - 1) * (E - 1) > 0 ? (P - 1) * (E - 1) : 1;
+  c2<T> w[NT];
+  // tw: the table of this axis (length L) in double
+  __device__ __forceinline__ void load(int t, const double2* __restrict__ tw) {
+    int ns = first_radix<L, E>();
+#pragma unroll
+    for (int p = 1; p < P; ++p) {
+      const int k = (t & (ns * W - 1)) / W;
+      const double2 w1 = tw[k * (L / (ns * E))];
+      double2 wr = w1;
+#pragma unroll
+      for (int r = 1; r < E; ++r) {
+        w[(p - 1) * (E - 1) + (r - 1)] = rnd<T>(wr);
+        wr = dmul(wr, w1);
+      }
+      ns *= E;
+    }
+  }
+};
+
+// One pass; NS is the number of points combined so far along l (radix R = E
+// unless NS = 1).
+template <typename T, int N, int W, int E, int R, int NS, bool INV, bool LAST, int LS>
+__device__ __forceinline__ void axis_pass(c2<T>* v, int t, c2<T>* lds, const c2<T>* tw) {
+  constexpr int TEAM = N / E;
+  constexpr int BPL = E / R;
+#pragma unroll
+  for (int b = 0; b < BPL; ++b) {
+    const int j = t + TEAM * b;
+    const int k = j & (NS * W - 1);
+    c2<T> x[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) x[r] = v[b + r * BPL];
+    if constexpr (NS > 1) {
+      static_assert(R == E && BPL == 1, "twiddled passes are radix E");
+#pragma unroll
+      for (int r = 1; r < R; ++r) x[r] = INV ? cmulc<T>(x[r], tw[r - 1]) : cmul<T>(x[r], tw[r - 1]);
+    }
+    Dft<T, R, INV>::run(x);
+    if constexpr (LAST) {
+#pragma unroll
+      for (int r = 0; r < R; ++r) v[b + r * BPL] = x[r];
+    } else {
+      const int base = (j - k) * R + k;
+#pragma unroll
+      for (int r = 0; r < R; ++r) lds[pad(base + r * NS * W) * LS] = x[r];
+    }
+  }
+}
+
+// The passes of one axis, work-group teams with two exchange areas in turn
+// (`par`: parity of the exchanges made so far; see team_fft).
+template <typename T, int L, int W, int E, bool INV, int NS, int LS, int PI>
+struct AxisPasses {
+  static constexpr int N = L * W;
+  static constexpr int R = (NS == 1) ? first_radix<L, E>() : E;
+  static constexpr bool LAST = (NS * R == L);
+  __device__ __forceinline__ static void run(c2<T>* v, int t, c2<T>* lds, c2<T>* lds2, const c2<T>* twr, int par) {
+    c2<T>* area = ((PI + par) & 1) ? lds2 : lds;
+    axis_pass<T, N, W, E, R, NS, INV, LAST, LS>(v, t, area, twr + (PI > 0 ? (PI - 1) * (E - 1) : 0));
+    if constexpr (!LAST) {
+      constexpr int TEAM = N / E;
+      __syncthreads();
+#pragma unroll
+      for (int m = 0; m < E; ++m) v[m] = area[pad(t + TEAM * m) * LS];
+      AxisPasses<T, L, W, E, INV, NS * R, LS, PI + 1>::run(v, t, lds, lds2, twr, par);
+    }
+  }
+};
+template <typename T, int L, int W, int E, bool INV, int LS>
+__device__ __forceinline__ int axis_fft(c2<T>* v, int t, c2<T>* lds, c2<T>* lds2, const AxisTwiddles<T, L, W, E>& tw,
+                                        int par) {
+  AxisPasses<T, L, W, E, INV, 1, LS, 0>::run(v, t, lds, lds2, tw.w, par);
+  return par + AxisTwiddles<T, L, W, E>::P - 1;
+}
+
+// Change of the held order of an A x B array (i = a B + b) to its transpose
+// (i' = b A + a), one exchange.
+template <typename T, int A, int B, int E, int LS>
+__device__ __forceinline__ int transpose_held(c2<T>* v, int t, c2<T>* lds, c2<T>* lds2, int par) {
+  constexpr int TEAM = A * B / E;
+  c2<T>* area = (par & 1) ? lds2 : lds;
+#pragma unroll
+  for (int m = 0; m < E; ++m) area[pad(t + TEAM * m) * LS] = v[m];
+  __syncthreads();
+#pragma unroll
+  for (int m = 0; m < E; ++m) {
+    const int i = t + TEAM * m;  // = b A + a
+    v[m] = area[pad((i % A) * B + i / A) * LS];
+  }
+  return par + 1;
+}
+
 }  // namespace pf

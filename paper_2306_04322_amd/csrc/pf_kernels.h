@@ -90,6 +90,9 @@
 #ifndef PF_XROW_MIN_WAVES
 #define PF_XROW_MIN_WAVES 2  // register budget, register-form row pass (waves per SIMD)
 #endif
+#ifndef PF_COL2_MAX
+#define PF_COL2_MAX 4096  // 3D: most (y, z) points per column of the one-pass strided axes
+#endif
 #ifndef PF_COL_E_LONG_F32
 #define PF_COL_E_LONG_F32 8  // elements per lane, float column transforms of length >= 512
 #endif
@@ -1146,6 +1149,7 @@ struct ColArgs {
   const c2<T>* src;
   c2<T>* dst;
   const double2* tw;   // exp(-2 pi i q / N) for the transformed axis, double
+  const double2* tw2;  // col2_kernel: the same for z (tw: y)
   const T* kcol;       // |xi|^2 table indexed by the column (x frequency)
   const T* kaxis;      // |xi|^2 table of the transformed axis
   const T* kouter;     // |xi|^2 table indexed by the outer index (3D z pass), or null

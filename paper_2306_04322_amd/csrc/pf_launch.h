@@ -19,6 +19,7 @@ template <typename T> int row_launch(int nx, int p, const XArgs<T>& a, hipStream
 template <typename T, int P> int row_launch_exact(int nx, const XArgs<T>& a, hipStream_t s);
 template <typename T> int adj_row_launch(int nx, int p, const AdjArgs<T>& a, hipStream_t s);
 template <typename T> int col_launch(int n, int nouter, const ColArgs<T>& a, hipStream_t s);
+template <typename T> int col2_launch(int ny, int nz, const ColArgs<T>& a, hipStream_t s);
 template <typename T> int fd_fused_launch(int p, const FdArgs<T>& a, hipStream_t s);
 template <typename T> int fd_launch(int which, int p, const FdArgs<T>& a, hipStream_t s);
 int reduce_launch(const double* partials, int n, int width, double* out, const double* scale4,

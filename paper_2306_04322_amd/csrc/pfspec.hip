@@ -17,6 +17,20 @@
 
 using namespace pf;
 
+// 3D grids whose strided axes go in one pass (k_col2.inc): few points per (y, z)
+// plane, so that a work-group holds the planes of a few columns; above 1024
+// points its columns are one or two wide and pay only while there are few of
+// them.  FS step, four launches / two: FP32, F = 5: 16^3 13.3 / 8.3 us, 32^3 15.0 /
+// 10.5, 256 x 32 x 32 26.2 / 20.1, 1024 x 32 x 32 41.8 / 37.5, 64^3 26.0 / 24.8; but
+// 128 x 64 x 64 33.6 / 33.6, 256 x 64 x 64 43.5 / 53.4, F = 9: 256 x 32 x 64 42.0 /
+// 48.9, 64^3 32.1 / 32.9.  FP64, F = 5: 32^3 16.2 / 11.7, 1024 x 32 x 32 74.9 / 54.2,
+// 256 x 32 x 64 45.9 / 40.5, 64^3 32.8 / 30.0; F = 9: 64^3 41.6 / 43.8.
+static bool one_pass_strided(int nx, int rows, int F, bool f32) {
+  if (rows <= 1024) return true;
+  if (rows <= 2048) return !f32 || nx <= 128;
+  return rows <= PF_COL2_MAX && nx * F <= 320;
+}
+
 // 2D grids with the tiled x-spectrum layout (pf_kernels.h).  A compute unit
 // fetches whole 128-byte lines, of which a column work-group of two or four
 // columns used 16 or 32 bytes in the row-major layout; the row passes pay for
@@ -69,6 +83,7 @@ struct pf_handle {
   pf_config cfg;
   int nd, nx, ny, nz, F, p, nxh, rows;
   int rs, ts;     // row and tile stride of the x-spectra
+  bool col2;      // 3D: both strided axes in one pass (k_col2.inc)
   long long nyo;  // offset of the Nyquist values within an x-spectrum field
   long long P;
   size_t es;  // bytes per real element
@@ -256,9 +271,22 @@ ColArgs<T> cargs(const pf_handle* h, double dt) {
   return a;
 }
 
-// Strided-axis pass.  axis 1 = y, axis 2 = z.
+// Strided-axis pass.  axis 1 = y (with col2: y and z), axis 2 = z.
 template <typename T>
 pf_status col(pf_handle* h, ColArgs<T>& a, int axis, int* nblk) {
+  if (h->col2) {
+    a.ls = h->rs;
+    a.tw = twp<T>(h, 1);
+    a.tw2 = twp<T>(h, 2);
+    a.kaxis = ktp<T>(h, 1);
+    a.kouter = ktp<T>(h, 2);
+    const int pi = prof_begin(h, PROF_COL);
+    const int g = col2_launch<T>(h->ny, h->nz, a, h->stream);
+    prof_end(h, pi);
+    if (g < 0) return fail(PF_ERR_UNSUPPORTED, "column pass: unsupported lengths");
+    if (nblk) *nblk = g;
+    return check_launch("column pass");
+  }
   const long long plane = (long long)h->ny * h->rs;  // (3D: row-major)
   int n, nouter;
   if (axis == 1) {
@@ -316,7 +344,7 @@ pf_status spectral_update(pf_handle* h, double dt, bool first, int nrec) {
   ColArgs<T> a = cargs<T>(h, dt);
   a.first = first ? 1 : 0;
   a.nrec = nrec;
-  if (h->nd == 2) {
+  if (h->nd == 2 || h->col2) {
     a.src = specB<T>(h);
     a.dst = specS<T>(h);
     a.mode = COL_UPDATE;
@@ -462,7 +490,7 @@ pf_status energy_run(pf_handle* h, int scheme, double out[5]) {
     a.src = specB<T>(h);
     a.dst = specB<T>(h);
     int ng = 0;
-    if (h->nd == 3) {
+    if (h->nd == 3 && !h->col2) {
       a.mode = COL_FWD;
       PF_TRY(col<T>(h, a, 1, nullptr));
       a.mode = COL_ENERGY;
@@ -545,7 +573,7 @@ pf_status adjoint_run(pf_handle* h, double dt, long long k, const T* u0, T* lam,
   for (long long n = k - 1; n >= 0; --n) {
     ColArgs<T> a = cargs<T>(h, dt);
     a.src = specB<T>(h);
-    if (h->nd == 2) {
+    if (h->nd == 2 || h->col2) {
       a.dst = specS<T>(h);
       a.mode = COL_ADJ;
       PF_TRY(col<T>(h, a, 1, nullptr));
@@ -624,7 +652,7 @@ pf_status time_pass_run(pf_handle* h, int pass, int reps, double* avg_ms) {
     a.src = specB<T>(h);
     a.dst = specS<T>(h);
     a.mode = COL_UPDATE;
-    return col<T>(h, a, h->nd == 2 ? 1 : 2, nullptr);
+    return col<T>(h, a, h->nd == 2 || h->col2 ? 1 : 2, nullptr);
   };
   PF_TRY(launch());
   hipEvent_t e0, e1;
@@ -693,10 +721,11 @@ pf_status pf_create(const pf_config* cfg, pf_handle** out) {
   // (and planes) are not padded: no gain was measured there.
   const int ktile = c.prec == PF_F32 ? KTile<float>::N : KTile<double>::N;
   h->rows = h->ny * h->nz;
-  if (tiled_layout(c.ndim, h->nx, h->ny, c.p, c.prec == PF_F32)) {
+  h->col2 = c.ndim == 3 && one_pass_strided(h->nx, h->rows, h->F, c.prec == PF_F32);
+  if (h->col2 || tiled_layout(c.ndim, h->nx, h->ny, c.p, c.prec == PF_F32)) {
     h->rs = ktile;
-    h->ts = ktile * h->ny;
-    h->nyo = (long long)(h->nx / 2) * h->ny;
+    h->ts = ktile * h->rows;
+    h->nyo = (long long)(h->nx / 2) * h->rows;
   } else {
     h->rs = (h->nx / 2 + align_c - 1) / align_c * align_c;
     if (c.ndim == 2 && !(c.prec == PF_F32 && h->nx == 4096)) h->rs += align_c;
