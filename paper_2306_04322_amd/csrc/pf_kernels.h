@@ -437,7 +437,8 @@ __device__ __forceinline__ void wave_c2r_pre(c2<T>* v, const c2<T>* __restrict__
 #pragma unroll
   for (int m = 0; m < E; ++m) {
     const int k = t + TEAM * m;
-    const c2<T> Y = conj<T>(STAGE ? ar[pad(NH - k)] : (k == 0 ? *nyq : src[rm.mirror(m)]));
+    const c2<T> Y = conj<T>(STAGE ? ar[pad(NH - k)]
+                                  : (k == 0 ? *nyq : LIN ? src[(NH - k) & (NH - 1)] : src[rm.mirror(m)]));
     const c2<T> sm = add<T>(X[m], Y);
     const c2<T> d = cmulc<T>(sub<T>(X[m], Y), lt.w[m]);  // * exp(+2 pi i k / NX)
     v[m] = mk<T>(sm.x - d.y, sm.y + d.x);
@@ -595,7 +596,9 @@ rowpass_kernel(XArgs<T> a) {
   const int lane = tid & 63;
   const int unit = lane / TEAM;
   const int t = lane - unit * TEAM;
-  const int row0 = row_block<T>(a.ts) * ROWS;
+  // (LIN is known to be row-major, and its address for kx = 0 stays in the row:
+  // 1024^2 FP32 row pass 12.57 -> 12.15 us against the general forms)
+  const int row0 = (G::LIN ? int(blockIdx.x) : row_block<T>(a.ts)) * ROWS;
   const RowMap<T, NH, E, G::LIN> rm(t, a.ts, 0);
   const int F = FEK >= 0 ? PMAX + 1 : a.F;  // the fixed-kind instantiations have p = PMAX
   const int p = F - 1;
@@ -966,7 +969,7 @@ adjrow_kernel(AdjArgs<T> a) {
   const int lane = tid & 63;
   const int unit = lane / TEAM;
   const int t = lane - unit * TEAM;
-  const int row0 = row_block<T>(a.ts) * ROWS;
+  const int row0 = (G::LIN ? int(blockIdx.x) : row_block<T>(a.ts)) * ROWS;
   const RowMap<T, NH, E, G::LIN> rm(t, a.ts, 0);
   constexpr int F = PMAX + 1;
   const int p = F - 1;
