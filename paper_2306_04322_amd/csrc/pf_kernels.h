@@ -6,10 +6,11 @@
 //                 r rs + koff(kx); the Nyquist values kx = Nx/2 of all rows
 //                 follow as one array (offset nyo in the field), contiguous
 //                 along y.  Row-major: koff(kx) = kx, rs = Sx (a 128-byte
-//                 multiple).  Tiled (2D, long columns): tiles of KTile columns
-//                 (32 bytes) one after the other, each [Ny][KTile], so a
-//                 column work-group reads and writes contiguous memory and a
-//                 row work-group of R rows pieces of 32 R bytes.
+//                 multiple).  Tiled (2D with long columns, 3D with small
+//                 planes): tiles of KTile columns (32 bytes) one after the
+//                 other, each [Nz][Ny][KTile], so a column work-group reads
+//                 and writes contiguous memory and a row work-group of R rows
+//                 pieces of 32 R bytes.
 // A "row" is one (z, y) line along x; rows = Ny * Nz.  Keeping the Nyquist
 // column apart lets the strided passes cover kx < Nx/2 with full tiles and
 // the Nyquist column with a few items that take many outer rows at once
@@ -30,9 +31,10 @@
 // 3D) for a tile of C consecutive x-spectrum columns.  Lanes are laid out
 // column-fastest so every global access of a wavefront covers contiguous
 // row segments of C values (128 bytes on axes shorter than 512 points, 16
-// or 32 bytes on the longer ones, where tiles are narrower).  Modes: forward only, inverse only, the k-space
-// update of Eq. (12)-(15) between a forward and an inverse transform, the
-// adjoint multipliers, and the spectral gradient-energy sums.
+// or 32 bytes on the longer ones, where tiles are narrower).  Modes: forward
+// only, inverse only, the k-space update of Eq. (12)-(15) between a forward
+// and an inverse transform, the adjoint multipliers, and the spectral
+// gradient-energy sums.  3D grids with small planes take k_col2.inc instead.
 #pragma once
 
 #include <hip/hip_runtime.h>
