@@ -533,8 +533,9 @@ struct PairMap {
 // SM selects the form for grids with few rows: as many rows as one wavefront
 // has room for (one where a row's F transforms fill it), which spreads a
 // small grid over more compute units than 1024-point work-groups would.
-// TL selects the form for the tiled layout where there is one (TWO).
-template <typename T, int NX, int PMAX, bool SM = false, bool TL = false>
+// TL selects the form for the tiled layout where there is one (TWO), ADJ the
+// adjoint's.
+template <typename T, int NX, int PMAX, bool SM = false, bool TL = false, bool ADJ = false>
 struct RGeom {
   static constexpr int NH = NX / 2;
   static constexpr int E = NH >= 512 ? (NH / 64 < 16 ? NH / 64 : 16) : (NH < 8 ? NH : 8);
@@ -550,9 +551,15 @@ struct RGeom {
   // over 4) evenly over the CU's SIMDs; measured faster at Nx = 1024 (four
   // rows) and 2048 (two rows) only.  (The forward row pass now takes the
   // register form at 2048 points; the adjoint row pass keeps this one.)
+  // ADJ: the adjoint's pointwise phase needs more than the 128 registers a lane
+  // has in a work-group of 1024: with four 1024-point rows it kept 64 (p = 2)
+  // to 400 bytes (p = 6) per lane in scratch, with one row none (four adjoint
+  // steps with their recomputation, FP32, four rows / one: 1024^2 p = 3 421 / 360
+  // us, p = 4 534 / 410, p = 6 744 / 496; 1024 x 16 p = 4 257 / 180; 1024 x 256 x 16
+  // p = 6 3172 / 2227; two rows as one).
   static constexpr int SM_ROWS = UPW > PMAX ? 1 << ilog2(UPW / (PMAX + 1)) : 1;
   static constexpr int BASE_ROWS = SM ? SM_ROWS : (NX >= 1024 ? 1 : 1024 / NX);
-  static constexpr int MULT_WANT = NX == 2048 ? PF_ROW_MULT_2048 : NX == 1024 ? (TL ? 2 : PF_ROW_ROWS_LONG) : PF_ROW_MULT_SHORT;
+  static constexpr int MULT_WANT = NX == 2048 ? PF_ROW_MULT_2048 : NX == 1024 ? (TL ? 2 : ADJ ? 1 : PF_ROW_ROWS_LONG) : PF_ROW_MULT_SHORT;
   static constexpr bool MULTI = !SM && NX <= 2048 && sizeof(T) == 4 && PF_ROW_NW > 0 && MULT_WANT > 1 &&
                                 PF_ROW_NW * MULT_WANT <= 16 &&
                                 MULT_WANT * BASE_ROWS * ROW_BYTES <= 160 * 1024;
@@ -958,9 +965,9 @@ adj_row_kernel(AdjArgs<T> a) {
 // e_i; the pointwise phase overwrites slots 0 and 2 + i with lambda^n for the
 // forward transforms of phase 3.  The order-parameter count is PMAX.
 template <typename T, int NX, int PMAX, bool SM, bool TL>
-__global__ void __attribute__((amdgpu_flat_work_group_size(1, RGeom<T, NX, PMAX, SM, TL>::WG)))
+__global__ void __attribute__((amdgpu_flat_work_group_size(1, RGeom<T, NX, PMAX, SM, TL, true>::WG)))
 adjrow_kernel(AdjArgs<T> a) {
-  using G = RGeom<T, NX, PMAX, SM, TL>;
+  using G = RGeom<T, NX, PMAX, SM, TL, true>;
   constexpr int NH = G::NH, E = G::E, TEAM = G::TEAM, UPW = G::UPW, ROWS = G::ROWS;
   constexpr int NW = G::NW, SL = G::SLOTS, WG = G::WG, SC = G::SLOT_C;
   static_assert(G::FITS, "adjoint row pass v2 does not fit this size");
