@@ -39,6 +39,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "pf_fe.h"
 #include "pf_fft.h"
 
@@ -147,13 +149,16 @@ struct RowMap {
     hi = base + koff<T>(NH - t, ts);
     step = unsigned(TEAM / KTile<T>::N) * unsigned(ts);
   }
-  __device__ __forceinline__ unsigned at(int m) const {
-    if constexpr (LIN) return base + t + TEAM * m;
+  // (row-major: signed, so that the m part goes into the instruction's offset:
+  // 512 x 64 x 64, F = 3, FP64 step 89.9 -> 85.9 us)
+  using off_t = std::conditional_t<LIN, int, unsigned>;
+  __device__ __forceinline__ off_t at(int m) const {
+    if constexpr (LIN) return int(base) + t + TEAM * m;
     else if constexpr (STEP) return lo + m * step;
     else return base + koff<T>(t + TEAM * m, ts);
   }
-  __device__ __forceinline__ unsigned mirror(int m) const {  // (not for kx = 0)
-    if constexpr (LIN) return base + NH - t - TEAM * m;
+  __device__ __forceinline__ off_t mirror(int m) const {  // (not for kx = 0)
+    if constexpr (LIN) return int(base) + NH - t - TEAM * m;
     else if constexpr (STEP) return hi - m * step;
     else return base + koff<T>(NH - t - TEAM * m, ts);
   }
@@ -199,6 +204,11 @@ struct XGeom {
   // 2048 x 1024, where one-row work-groups balance better)
   static constexpr int ROWS = TEAM >= 64 ? (TL && TEAM < 256 ? 256 / TEAM : 1) : 64 / TEAM;
   static constexpr int WG = ROWS * TEAM;
+  // rows of up to 256 points have a form for each layout: this one is only
+  // launched on the row-major layout, and as a lane's addresses are then known to
+  // be consecutive, 8- and 16-point rows go in wide accesses (16 x 512 x 512, F = 3,
+  // FP32 step 166 us with the general addresses, 150 us; one-step call 218 / 198)
+  static constexpr bool LIN = !TL && NX <= 256;
   static constexpr int REGION = lds_span(NH) + 1;  // LDS complex values per team
   // register budget of the fixed-flag instantiations: two work-groups per
   // SIMD where a work-group has at most one wavefront per SIMD (with up to
@@ -210,9 +220,9 @@ struct XGeom {
 // xn = X_NH (lane t = 0; zero elsewhere and for inactive rows).  Issued for
 // all fields of a row before the first transform, so their latencies
 // overlap.
-template <typename T, int NX, int E>
+template <typename T, int NX, int E, bool LIN>
 __device__ __forceinline__ void row_load(c2<T>* v, c2<T>& xn, const c2<T>* __restrict__ src,
-                                         const RowMap<T, NX / 2, E>& rm, const c2<T>* __restrict__ nyq,
+                                         const RowMap<T, NX / 2, E, LIN>& rm, const c2<T>* __restrict__ nyq,
                                          bool active, int t) {
 #pragma unroll
   for (int m = 0; m < E; ++m) v[m] = active ? src[rm.at(m)] : mk<T>(T(0), T(0));
@@ -246,8 +256,8 @@ __device__ __forceinline__ void row_c2r(c2<T>* v, c2<T> xn, int t, c2<T>* my,
 
 // R2C of one row held as v[m] = (x[2k], x[2k+1]); writes X[0..NH-1] to dst
 // (at the offsets of rm) and X[NH] to *nyq.
-template <typename T, int NX, int E>
-__device__ __forceinline__ void row_r2c(c2<T>* v, c2<T>* __restrict__ dst, const RowMap<T, NX / 2, E>& rm,
+template <typename T, int NX, int E, bool LIN>
+__device__ __forceinline__ void row_r2c(c2<T>* v, c2<T>* __restrict__ dst, const RowMap<T, NX / 2, E, LIN>& rm,
                                         c2<T>* __restrict__ nyq, bool active, int t,
                                         c2<T>* my, const LaneTwiddles<T, NX / 2, E>& lt,
                                         const Twiddles<T, NX / 2, E>& tws) {
@@ -291,15 +301,15 @@ xpass_kernel(XArgs<T> a) {
   // with the tiled layout lanes go in pieces of KTile, the rows' pieces in turn,
   // so a wavefront's accesses cover R x KTile contiguous values
   constexpr int KT = TEAM % KTile<T>::N == 0 ? KTile<T>::N : TEAM;
-  const bool tl = a.ts != KTile<T>::N;
+  const bool tl = !G::LIN && a.ts != KTile<T>::N;
   const int lane = threadIdx.x;
   const int team = ROWS == 1 ? 0 : tl ? (lane / KT) % ROWS : lane / TEAM;
   const int t = ROWS == 1 ? lane : tl ? lane / (KT * ROWS) * KT + lane % KT : lane % TEAM;
-  const int row0 = row_block<T>(a.ts) * ROWS;
+  const int row0 = (G::LIN ? int(blockIdx.x) : row_block<T>(a.ts)) * ROWS;
   const int row = row0 + team;
   const bool active = row < a.rows;
   const long long rrow = active ? row : 0;
-  const RowMap<T, NH, E> rm(t, a.ts, unsigned(team) * unsigned(a.rs));
+  const RowMap<T, NH, E, G::LIN> rm(t, a.ts, unsigned(team) * unsigned(a.rs));
   c2<T>* my = lds + team * G::REGION;
   const int F = FEK >= 0 ? PMAX + 1 : a.F;
   const int p = F - 1;

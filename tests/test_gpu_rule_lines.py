@@ -1,0 +1,48 @@
+"""GPU parity at the lines between the forms that the launchers choose from
+(k_row.inc, pfspec.hip), where no other test reaches both sides: FS steps in
+calls of one and of several steps, and the spectral energy.
+
+Tolerances as for the same checks on other shapes: FS FP64 1e-11, FP32 2e-5
+relative L2 per field; energy FP64 1e-12, FP32 2e-6 of each part (or of a
+thousandth of the total)."""
+
+import numpy as np
+import pytest
+
+from oracle import energy as oen
+from oracle import fs as ofs
+from paper_2306_04322_amd import inputs as I
+from parity_util import DISTINCT, announce, fp32_rounded, gpu_or_fail, max_rel, rel_l2
+
+pytestmark = pytest.mark.gpu
+
+
+def _check(n, p, prec, fe=I.PAPER_FE):
+    gpu_or_fail()
+    from paper_2306_04322_amd.pfspec import Solver
+    ndim = len(n)
+    cfg = I.make_config(ndim, n, (1.0, 0.9, 1.1)[:ndim], p, fe, **DISTINCT)
+    u0 = I.random_ic(cfg, seed=61)
+    u0[1:] = 0.5 * u0[1:] + 0.3 * np.arange(1, p + 1).reshape((p,) + (1,) * ndim) / p
+    if prec == "f32":
+        u0 = fp32_rounded(u0)
+    announce("rule lines", n, p, prec)
+    s = Solver(cfg, prec)
+    s.set_fields(u0)
+    e, ref = s.energy("fs"), oen.energy(u0, cfg, "fs")
+    tol = 1e-12 if prec == "f64" else 2e-6
+    for i in range(5):
+        assert abs(e[i] - ref[i]) <= tol * max(abs(ref[i]), 1e-3 * abs(ref[0])), (i, e, ref)
+    s.step_fs(0.01, 2)
+    s.step_fs(0.01, 1)
+    errs = rel_l2(s.get_fields(), ofs.fs_run(u0, cfg, 0.01, 3))
+    assert max_rel(errs) <= (1e-11 if prec == "f64" else 2e-5), errs
+
+
+@pytest.mark.parametrize("prec", ["f64", "f32"])
+@pytest.mark.parametrize("n,p", [((256, 2048), 1), ((256, 4096), 1), ((128, 4096), 5), ((256, 2048), 5),
+                                 ((256, 32, 64), 5), ((8, 512, 256), 1), ((16, 512, 256), 1), ((128, 128, 128), 1)])
+def test_register_form_layouts(n, p, prec):
+    """Rows of up to 256 points in the register form, on tiled and on
+    row-major x-spectra, and their neighbours in the wave form."""
+    _check(n, p, prec)
