@@ -46,3 +46,10 @@ def test_register_form_layouts(n, p, prec):
     """Rows of up to 256 points in the register form, on tiled and on
     row-major x-spectra, and their neighbours in the wave form."""
     _check(n, p, prec)
+
+
+@pytest.mark.parametrize("n,p", [((1024, 8), 5), ((1024, 512), 5), ((1024, 512), 6), ((1024, 1024), 5)])
+def test_long_float_rows_few(n, p):
+    """1024-point float rows with more than four order parameters: one row
+    per work-group on grids with few rows, four on the first grid beyond."""
+    _check(n, p, "f32")
