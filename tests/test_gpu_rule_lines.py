@@ -53,3 +53,12 @@ def test_long_float_rows_few(n, p):
     """1024-point float rows with more than four order parameters: one row
     per work-group on grids with few rows, four on the first grid beyond."""
     _check(n, p, "f32")
+
+
+@pytest.mark.parametrize("n,p,prec", [((8, 32), 1, "f64"), ((16, 16), 1, "f64"), ((256, 64), 1, "f64"),
+                                      ((32, 64, 128), 1, "f64"), ((8, 256, 256), 2, "f32"), ((256, 2048), 8, "f32"),
+                                      ((32, 128, 128), 4, "f64")])
+def test_first_and_energy_pass(n, p, prec):
+    """Grids whose first pass and energy pass take another form than their
+    steady-state pass."""
+    _check(n, p, prec)
