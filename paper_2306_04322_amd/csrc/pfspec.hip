@@ -19,16 +19,22 @@ using namespace pf;
 
 // 3D grids whose strided axes go in one pass (k_col2.inc): few points per (y, z)
 // plane, so that a work-group holds the planes of a few columns; above 1024
-// points its columns are one or two wide and pay only while there are few of
-// them.  FS step, four launches / two: FP32, F = 5: 16^3 13.3 / 8.3 us, 32^3 15.0 /
-// 10.5, 256 x 32 x 32 26.2 / 20.1, 1024 x 32 x 32 41.8 / 37.5, 64^3 26.0 / 24.8; but
-// 128 x 64 x 64 33.6 / 33.6, 256 x 64 x 64 43.5 / 53.4, F = 9: 256 x 32 x 64 42.0 /
-// 48.9, 64^3 32.1 / 32.9.  FP64, F = 5: 32^3 16.2 / 11.7, 1024 x 32 x 32 74.9 / 54.2,
-// 256 x 32 x 64 45.9 / 40.5, 64^3 32.8 / 30.0; F = 9: 64^3 41.6 / 43.8.
+// points a work-group holds one column, which pays only while there are few of
+// them.  FS step, four launches / two, us:
+//   up to 1024 points, F = 5: FP32 16^3 13.3 / 8.3, 32^3 15.0 / 10.5, 1024 x 32 x 32
+//   41.8 / 37.5; FP64 32^3 16.2 / 11.7, 1024 x 32 x 32 74.9 / 54.2
+//   up to 2048, FP32 (64 x 32 planes): nx = 8 a third less for every F; nx = 128,
+//   F = 2 .. 9, 1.07 to 1.25 times as fast (one-step call 1.00 to 1.12); nx = 256
+//   1.07 (F = 2) to 0.87 (F = 9); nx = 512 0.90 to 0.79.
+//   FP64: nx = 512 1.09 (F = 2) to 1.00 (F = 9); nx = 1024 1.05, 1.05, 1.03 (F = 2 .. 4),
+//   1.01 with the one-step call 0.93 (F = 5 .. 7), 0.90 (F = 8), 0.94 (F = 9)
+//   up to 4096 (64 x 64 planes): FP32 64^3 1.02 to 1.15 (F = 2 .. 8), 0.98 (F = 9); 128 x
+//   64 x 64 0.92 to 1.11.  FP64 64^3 1.03 to 1.20 (F = 2 .. 7), 0.97 (F = 9); nx <= 32
+//   with F < 4 0.94 to 1.00 (one-step call 0.86 to 0.95), with F >= 4 1.00 to 1.22
 static bool one_pass_strided(int nx, int rows, int F, bool f32) {
   if (rows <= 1024) return true;
-  if (rows <= 2048) return !f32 || nx <= 128;
-  return rows <= PF_COL2_MAX && nx * F <= 320;
+  if (rows <= 2048) return f32 ? nx <= 128 : nx * F <= 4608;
+  return rows <= PF_COL2_MAX && nx * F <= 320 && (f32 || nx > 32 || F >= 4);
 }
 
 // 2D grids with the tiled x-spectrum layout (pf_kernels.h).  A compute unit

@@ -62,3 +62,12 @@ def test_first_and_energy_pass(n, p, prec):
     """Grids whose first pass and energy pass take another form than their
     steady-state pass."""
     _check(n, p, prec)
+
+
+@pytest.mark.parametrize("n,p,prec", [((1024, 32, 64), 3, "f64"), ((1024, 64, 32), 4, "f64"), ((512, 16, 128), 8, "f64"),
+                                      ((128, 64, 32), 8, "f32"), ((256, 64, 32), 1, "f32"), ((32, 64, 64), 2, "f64"),
+                                      ((32, 64, 64), 3, "f64"), ((8, 64, 64), 2, "f32"), ((32, 64, 64), 8, "f32"),
+                                      ((64, 64, 64), 1, "f64")])
+def test_one_pass_strided_lines(n, p, prec):
+    """3D grids on both sides of the one-pass strided axes' rule."""
+    _check(n, p, prec)
