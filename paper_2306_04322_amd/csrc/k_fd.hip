@@ -1005,19 +1005,22 @@ static int fd3_march(const FdArgs<T>& a, hipStream_t s) {
 // One step in one launch; 0 where the two-kernel step is taken.
 // 2D: always fused (1024^2, F = 5, FP32 14.9 -> 11.8 us per step, 256^2 6.9 ->
 // 3.6, 4096^2 220 -> 169; FP64 22.6 -> 19.4, 7.4 -> 4.3, 407 -> 309).
-// 3D, from PF_FD3_MARCH_MB of fields (half of that where the planes of all
-// fields take at most 12 registers, which leaves room for the prefetch):
-// marching, in 512-lane work-groups with prefetch where a float row fits 64
-// lanes, else in 768-lane ones (256^3, F = 5, FP32 138 against 159 us; 512 x
-// 256 x 256 has rows for the latter only).  Below that the marching
-// work-groups are too few (128^3, F = 5, FP32 28.5 us against 25.9 of the two
-// kernels).
+// 3D, from PF_FD3_MARCH_MB of fields (half of that with at most two order
+// parameters, whose short steps the second launch costs more: 64 x 256 x 256, F = 3,
+// FP32 31.8 -> 28.6 us; but F = 6, 32 x 256 x 256, 48 MB, FP32 29.3 -> 31.4): marching,
+// in 512-lane work-groups with prefetch where a float row fits 64 lanes, else in
+// 768-lane ones (256^3, F = 5, FP32 138 against 159 us; 512 x 256 x 256 has rows for
+// the latter only).  Below that the marching work-groups are too few (128^3, F =
+// 5, FP32 28.5 us against 25.9 of the two kernels).
 // 3D, up to PF_FD3_TILE_MB of fields, or 128-point float rows with at most
-// four order parameters: tiles (32^3, F = 5, FP32 7.4 -> 3.9 us, 64^3 9.3 ->
-// 6.1, 128^3 25.9 -> 24.9; but 64 x 128^2, 21 MB: 16.3 -> 17.4; FP64 64^3 10.1
-// -> 7.4, 32 x 128^2, 21 MB: 15.1 -> 17.7).  64-point double rows with more
-// than five order parameters spill (64^3, p = 8: 14.2 -> 23.7 us) and stay
-// with the two kernels.
+// four order parameters below PF_FD3_MARCH_MB / 2: tiles (32^3, F = 5, FP32 7.4 ->
+// 3.9 us, 64^3 9.3 -> 6.1, 128^3 25.9 -> 24.9; but 64 x 128^2, 21 MB: 16.3 -> 17.4, 128
+// x 256 x 128, F = 5, FP32, 84 MB 46 -> 52; FP64 64^3 10.1 -> 7.4, 32 x 128^2, 21 MB: 15.1
+// -> 17.7).  16- and 32-point rows go by one point per thread and leave the tiles
+// a little earlier (FP32 32 x 256 x 128, F = 2, 8 MB 10.6 -> 11.9, 32 x 128^2, F = 3, 6
+// MB 8.8 -> 7.9; FP64 32 x 64 x 128, F = 5, 10 MB 9.9 -> 10.5, F = 4, 8 MB 9.8 -> 9.1).
+// 64-point double rows with more than five order parameters spill (64^3, p = 8:
+// 14.2 -> 23.7 us) and stay with the two kernels.
 #ifndef PF_FD3_MARCH_MB
 #define PF_FD3_MARCH_MB 96
 #endif
@@ -1037,16 +1040,17 @@ static int fd_fused(const FdArgs<T>& a, hipStream_t s) {
   constexpr int VM = P > 4 ? VMAX / 2 : VMAX;  // vectors that leave room in registers
   constexpr int words = (P + 1) * VM * int(sizeof(T)) / 4;
   const long long mb = ((long long)a.F * a.P * sizeof(T)) >> 20;
-  if (mb >= (words <= 12 ? PF_FD3_MARCH_MB / 2 : PF_FD3_MARCH_MB)) {
+  if (mb >= (P <= 2 ? PF_FD3_MARCH_MB / 2 : PF_FD3_MARCH_MB)) {
     if constexpr (sizeof(T) == 4 && words > 12) {
       if (a.nx / VM <= 64) return fd3_march<T, P, VM, 512, true>(a, s);
     }
     return fd3_march<T, P, VM, 768, (words <= 12)>(a, s);
   }
   if constexpr (VMAX == 4 && P <= 4) {
-    if (a.nx == 128) return fd3_tile_go<T, P, 4, 4, 4>(a, s);
+    if (a.nx == 128 && mb < PF_FD3_MARCH_MB / 2) return fd3_tile_go<T, P, 4, 4, 4>(a, s);
   }
-  if (mb >= PF_FD3_TILE_MB) return 0;
+  const bool scalar_rows = a.nx == 16 || a.nx == 32;
+  if (mb >= (scalar_rows ? (sizeof(T) == 4 ? PF_FD3_TILE_MB - 3 : PF_FD3_TILE_MB - 1) : PF_FD3_TILE_MB)) return 0;
   if (a.nx <= 8) return fd3_tile_go<T, P, 1, 8, 8>(a, s);   // 96 rows of 8 lanes
   if (a.nx <= 16) return fd3_tile_go<T, P, 1, 4, 8>(a, s);  // 56 of 16
   if (a.nx <= 32) return fd3_tile_go<T, P, 1, 4, 4>(a, s);  // 32 of 32
