@@ -1,4 +1,7 @@
-"""GPU parity of the FD step with the oracle on both sides of the 3D
+"""GPU parity of the FD step with the oracle where no other test reaches: the
+marching form with more than four order parameters (half the vector width), in
+both precisions and both work-group sizes, and with a last block of planes cut
+off by the grid; the Landau polynomial in every form; both sides of the 3D
 rule's lines (k_fd.hip).
 
 Tolerance: as for the FD step's other parity tests (FP64 1e-12, FP32 1e-5
@@ -13,9 +16,16 @@ from parity_util import DISTINCT, announce, fp32_rounded, gpu_or_fail, max_rel, 
 
 pytestmark = pytest.mark.gpu
 
+# FP32: 512 lanes with prefetch (p = 8, 6), 768 lanes (p = 8 and 5, prefetch);
+# FP64: 768 lanes (p = 8, 5)
+MARCH = [((128, 128, 256), 8, "f32"), ((64, 256, 256), 6, "f32"), ((256, 128, 128), 8, "f32"), ((128, 256, 128), 5, "f32"),
+         ((128, 128, 128), 8, "f64"), ((64, 256, 128), 5, "f64")]
 # the two-kernel step below the marching form's line, tiles below theirs
 LINES = [((64, 128, 256), 5, "f32"), ((128, 256, 128), 4, "f32"), ((32, 256, 128), 1, "f32"), ((32, 128, 128), 1, "f32"),
          ((16, 128, 128), 4, "f64"), ((32, 64, 128), 3, "f64"), ((64, 256, 128), 2, "f64")]
+# 2D tiles, 3D tiles, marching and the two-kernel step
+POLY = [((64, 16), 3, "f32"), ((512, 8), 2, "f64"), ((16, 16, 8), 2, "f32"), ((64, 8, 8), 5, "f64"), ((128, 8, 8), 4, "f32"),
+        ((256, 128, 128), 2, "f32"), ((128, 128, 256), 3, "f64"), ((256, 16, 8), 6, "f32")]
 
 
 def _check(n, p, prec, fe, dt, steps):
@@ -35,6 +45,12 @@ def _check(n, p, prec, fe, dt, steps):
     assert max_rel(errs) <= (1e-12 if prec == "f64" else 1e-5), errs
 
 
-@pytest.mark.parametrize("n,p,prec", LINES)
+@pytest.mark.parametrize("n,p,prec", MARCH + LINES)
 def test_fd_large(n, p, prec):
     _check(n, p, prec, I.PAPER_FE, 2e-4, 2)
+
+
+@pytest.mark.parametrize("n,p,prec", POLY)
+def test_fd_polynomial(n, p, prec):
+    assert all(I.POLY_FE[k] != 0.0 for k in ("A", "B", "D", "gamma", "delta", "eps"))
+    _check(n, p, prec, I.POLY_FE, 1e-4, 5 if np.prod(n) < 100000 else 2)
