@@ -3,6 +3,7 @@
 // include/pfspec.h.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -59,6 +60,20 @@ static bool tiled_layout(int ndim, int nx, int ny, int p, bool f32) {
   return ny >= 512 && few && nx >= 2048;
 }
 
+// FP64 grids with the tiled layout whose adjoint steps and whose spectral energy
+// are done row-major all the same (neither carries a spectrum from the FS steps):
+// their row passes are one row per work-group, pieces of 32 bytes in a tile, and
+// their column passes gain less.  Adjoint step, row-major / tiled, us: 4096 x 1024
+// p = 2 421 / 457, p = 6 1296 / 1377, 4096 x 2048 p = 2 836 / 892, 2048 x 1024 p = 6 498 /
+// 535, p = 8 742 / 813; but 4096 x 512 p = 2 218 / 212, 2048 x 1024 p = 4 285 / 281, 2048^2
+// p = 6 1022 / 1024.  Energy: 1024 x 4096 p = 4 238 / 271, p = 5 291 / 319, 1024 x 2048
+// p = 8 237 / 250; but 1024 x 4096 p = 3 164 / 156, 1024 x 2048 p = 7 186 / 182, 2048 x
+// 4096 p = 2 247 / 210.
+static bool adjoint_row_major(int nx, int ny, int p, bool f32) {
+  return !f32 && ((nx == 4096 && ny >= 1024) || (nx == 2048 && ny == 1024 && p >= 6));
+}
+static bool energy_row_major(int nx, int ny, int F, bool f32) { return !f32 && nx == 1024 && ny * F >= 18432; }
+
 namespace {
 
 thread_local std::string g_err;
@@ -83,14 +98,21 @@ struct ProfRec {
   int cls;
 };
 
+// Layout of the x-spectra (pf_kernels.h).
+struct SpecLayout {
+  int rs, ts;     // row and tile stride
+  long long nyo;  // offset of the Nyquist values within a field
+  size_t field;   // complex elements per field
+};
+
 }  // namespace
 
 struct pf_handle {
   pf_config cfg;
   int nd, nx, ny, nz, F, p, nxh, rows;
-  int rs, ts;     // row and tile stride of the x-spectra
-  bool col2;      // 3D: both strided axes in one pass (k_col2.inc)
-  long long nyo;  // offset of the Nyquist values within an x-spectrum field
+  SpecLayout lay;          // layout of the call being enqueued: the FS steps', or for a while
+  SpecLayout lay_adj, lay_en;  // the adjoint steps' and the spectral energy's (LayoutScope)
+  bool col2;               // 3D: both strided axes in one pass (k_col2.inc)
   long long P;
   size_t es;  // bytes per real element
   double M, kc, L, ke;
@@ -99,7 +121,6 @@ struct pf_handle {
   std::vector<double> tw[3], kt[3];
   // workspace layout (byte offsets)
   size_t off_B, off_S, off_C, off_tw[3], off_k[3], off_part, off_scal, ws_need;
-  size_t spec_field;  // complex elements per x-spectrum field
   long long nparts;
   std::vector<unsigned char> staging;
   void* fields = nullptr;
@@ -227,6 +248,14 @@ double* scal(const pf_handle* h) { return reinterpret_cast<double*>(h->ws + h->o
 // scalar slots in the workspace
 enum { SC_MEANC = 1, SC_EN = 4, SC_DPAR = 12 };
 
+// Another layout for the passes enqueued within a scope.
+struct LayoutScope {
+  pf_handle* h;
+  SpecLayout before;
+  LayoutScope(pf_handle* h_, const SpecLayout& l) : h(h_), before(h_->lay) { h->lay = l; }
+  ~LayoutScope() { h->lay = before; }
+};
+
 template <typename T>
 XArgs<T> xargs(const pf_handle* h) {
   XArgs<T> a;
@@ -234,11 +263,11 @@ XArgs<T> xargs(const pf_handle* h) {
   a.twx = twp<T>(h, 0);
   a.partials = partials(h);
   a.fs_real = h->P;
-  a.fs_spec = (long long)h->spec_field;
+  a.fs_spec = (long long)h->lay.field;
   a.rows = h->rows;
-  a.rs = h->rs;
-  a.ts = h->ts;
-  a.nyo = h->nyo;
+  a.rs = h->lay.rs;
+  a.ts = h->lay.ts;
+  a.nyo = h->lay.nyo;
   a.F = h->F;
   a.fe = fe_params<T>(h);
   return a;
@@ -262,11 +291,11 @@ ColArgs<T> cargs(const pf_handle* h, double dt) {
   a.mean_c = scal(h) + SC_MEANC;
   a.cstate = specC<T>(h);
   a.partials = partials(h);
-  a.fs_src = a.fs_dst = (long long)h->spec_field;
+  a.fs_src = a.fs_dst = (long long)h->lay.field;
   a.ncols = h->nx / 2;
   a.nyq = h->nx / 2;
-  a.nyo = h->nyo;
-  a.ts = h->ts;
+  a.nyo = h->lay.nyo;
+  a.ts = h->lay.ts;
   a.F = h->F;
   a.dtM = T(dt * h->M);
   a.dtMkc = T(dt * h->M * h->kc);
@@ -281,7 +310,7 @@ ColArgs<T> cargs(const pf_handle* h, double dt) {
 template <typename T>
 pf_status col(pf_handle* h, ColArgs<T>& a, int axis, int* nblk) {
   if (h->col2) {
-    a.ls = h->rs;
+    a.ls = h->lay.rs;
     a.tw = twp<T>(h, 1);
     a.tw2 = twp<T>(h, 2);
     a.kaxis = ktp<T>(h, 1);
@@ -293,11 +322,11 @@ pf_status col(pf_handle* h, ColArgs<T>& a, int axis, int* nblk) {
     if (nblk) *nblk = g;
     return check_launch("column pass");
   }
-  const long long plane = (long long)h->ny * h->rs;  // (3D: row-major)
+  const long long plane = (long long)h->ny * h->lay.rs;  // (3D: row-major)
   int n, nouter;
   if (axis == 1) {
     n = h->ny;
-    a.ls = h->rs;
+    a.ls = h->lay.rs;
     a.os = plane;
     a.nls = 1;  // Nyquist values: [z][y], contiguous along y
     a.nos = h->ny;
@@ -308,7 +337,7 @@ pf_status col(pf_handle* h, ColArgs<T>& a, int axis, int* nblk) {
   } else {
     n = h->nz;
     a.ls = plane;
-    a.os = h->rs;
+    a.os = h->lay.rs;
     a.nls = h->ny;
     a.nos = 1;
     nouter = h->ny;
@@ -485,6 +514,7 @@ pf_status energy_run(pf_handle* h, int scheme, double out[5]) {
   double* sc = scal(h) + SC_EN;
   const double dV = h->dV;
   if (scheme == 0) {
+    const LayoutScope scope(h, h->lay_en);
     XArgs<T> x = xargs<T>(h);
     x.u_in = static_cast<const T*>(h->fields);
     x.b_out = specB<T>(h);
@@ -569,6 +599,7 @@ pf_status adjoint_run(pf_handle* h, double dt, long long k, const T* u0, T* lam,
   PF_TRY(fs_run<T>(h, dt, k, u0, nullptr, store));
   const long long fsz = (long long)h->F * h->P;
   double* acc = scal(h) + SC_DPAR;
+  const LayoutScope scope(h, h->lay_adj);
   // first transform of lambda^k
   XArgs<T> x = xargs<T>(h);
   x.u_in = lam;
@@ -606,11 +637,11 @@ pf_status adjoint_run(pf_handle* h, double dt, long long k, const T* u0, T* lam,
     r.mean_c = scal(h) + SC_MEANC;
     r.partials = partials(h);
     r.fs_real = h->P;
-    r.fs_spec = (long long)h->spec_field;
+    r.fs_spec = (long long)h->lay.field;
     r.rows = h->rows;
-    r.rs = h->rs;
-    r.ts = h->ts;
-    r.nyo = h->nyo;
+    r.rs = h->lay.rs;
+    r.ts = h->lay.ts;
+    r.nyo = h->lay.nyo;
     r.F = h->F;
     r.do_fwd = n > 0 ? 1 : 0;
     r.first = n == k - 1 ? 1 : 0;
@@ -728,16 +759,22 @@ pf_status pf_create(const pf_config* cfg, pf_handle** out) {
   const int ktile = c.prec == PF_F32 ? KTile<float>::N : KTile<double>::N;
   h->rows = h->ny * h->nz;
   h->col2 = c.ndim == 3 && one_pass_strided(h->nx, h->rows, h->F, c.prec == PF_F32);
-  if (h->col2 || tiled_layout(c.ndim, h->nx, h->ny, c.p, c.prec == PF_F32)) {
-    h->rs = ktile;
-    h->ts = ktile * h->rows;
-    h->nyo = (long long)(h->nx / 2) * h->rows;
-  } else {
-    h->rs = (h->nx / 2 + align_c - 1) / align_c * align_c;
-    if (c.ndim == 2 && !(c.prec == PF_F32 && h->nx == 4096)) h->rs += align_c;
-    h->ts = ktile;
-    h->nyo = (long long)h->rows * h->rs;
-  }
+  const size_t nyq_field = (size_t(h->rows) + align_c - 1) / align_c * align_c;
+  SpecLayout rm, tl;
+  rm.rs = (h->nx / 2 + align_c - 1) / align_c * align_c;
+  if (c.ndim == 2 && !(c.prec == PF_F32 && h->nx == 4096)) rm.rs += align_c;
+  rm.ts = ktile;
+  rm.nyo = (long long)h->rows * rm.rs;
+  rm.field = size_t(rm.nyo) + nyq_field;
+  tl.rs = ktile;
+  tl.ts = ktile * h->rows;
+  tl.nyo = (long long)(h->nx / 2) * h->rows;
+  tl.field = size_t(tl.nyo) + nyq_field;
+  const bool f32 = c.prec == PF_F32;
+  const bool tiled2 = tiled_layout(c.ndim, h->nx, h->ny, c.p, f32);
+  h->lay = h->col2 || tiled2 ? tl : rm;
+  h->lay_adj = tiled2 && adjoint_row_major(h->nx, h->ny, c.p, f32) ? rm : h->lay;
+  h->lay_en = tiled2 && energy_row_major(h->nx, h->ny, h->F, f32) ? rm : h->lay;
   h->P = (long long)h->nx * h->ny * h->nz;
   h->M = c.M;
   h->kc = c.kappa_c;
@@ -752,14 +789,14 @@ pf_status pf_create(const pf_config* cfg, pf_handle** out) {
   }
   // workspace layout
   const size_t cbytes = 2 * h->es;
-  h->spec_field = size_t(h->nyo) + (size_t(h->rows) + align_c - 1) / align_c * align_c;
+  const size_t spec_field = std::max(h->lay.field, std::max(h->lay_adj.field, h->lay_en.field));
   size_t off = 0;
   h->off_B = off;
-  off = align256(off + size_t(h->F + 1) * h->spec_field * cbytes);
+  off = align256(off + size_t(h->F + 1) * spec_field * cbytes);
   h->off_S = off;
-  off = align256(off + size_t(h->F + 1) * h->spec_field * cbytes);
+  off = align256(off + size_t(h->F + 1) * spec_field * cbytes);
   h->off_C = off;
-  off = align256(off + h->spec_field * cbytes);
+  off = align256(off + spec_field * cbytes);
   for (int ax = 0; ax < 3; ++ax) {  // twiddle tables are double for both precisions
     h->off_tw[ax] = off;
     off = align256(off + size_t(ns[ax]) * 2 * sizeof(double));

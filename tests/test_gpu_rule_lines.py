@@ -71,3 +71,42 @@ def test_first_and_energy_pass(n, p, prec):
 def test_one_pass_strided_lines(n, p, prec):
     """3D grids on both sides of the one-pass strided axes' rule."""
     _check(n, p, prec)
+
+
+@pytest.mark.parametrize("n,p", [((1024, 2048), 8), ((1024, 2048), 7)])
+def test_energy_layout(n, p):
+    """Tiled FP64 grids whose spectral energy is done row-major, between FS
+    steps that are not, and a neighbour that keeps the tiles."""
+    _check(n, p, "f64")
+
+
+@pytest.mark.parametrize("n,p", [((4096, 1024), 1), ((2048, 1024), 6), ((2048, 1024), 1)])
+def test_adjoint_layout(n, p):
+    """Tiled FP64 grids whose adjoint steps are done row-major, with FS steps
+    before and after; tolerances as in the adjoint's other parity tests.  The
+    direction is the fields' deviation from their mean (no cancellation)."""
+    torch = gpu_or_fail()
+    from oracle import adjoint as oadj
+    from paper_2306_04322_amd.pfspec import Solver
+    cfg = I.make_config(2, n, (1.0, 0.9), p, I.PAPER_FE, **DISTINCT)
+    u0 = I.random_ic(cfg, seed=62)
+    u0[1:] = 0.5 * u0[1:] + 0.3 * np.arange(1, p + 1).reshape(p, 1, 1) / p
+    traj = oadj.trajectory(u0, cfg, 0.01, 2)
+    w = traj[-1] - traj[-1].mean(axis=(1, 2), keepdims=True)
+    announce("adjoint layout", n, p)
+    s = Solver(cfg, "f64")
+    s.set_fields(u0)
+    s.step_fs(0.01, 2)
+    lam = torch.as_tensor(w).to(s.device, s.dtype).contiguous()
+    ck = torch.as_tensor(u0).to(s.device, s.dtype).contiguous()
+    seg = s.segment_store(2)
+    dpar = s.adjoint_fs(0.01, 2, ck, lam, seg, np.zeros(4))
+    assert torch.equal(seg.view(-1)[-s.fields.numel():].view_as(s.fields), s.fields)  # same kernels as the forward call
+    rlam, rpar = oadj.fs_adjoint(traj, w, cfg, 0.01)
+    err = np.linalg.norm(lam.cpu().numpy() - rlam) / np.linalg.norm(rlam)
+    perr = np.max(np.abs(dpar - rpar) / np.abs(rpar))
+    print("lambda", err, "parameters", perr)
+    assert err <= 1e-10 and perr <= 1e-9
+    s.set_fields(u0)
+    s.step_fs(0.01, 2)
+    assert max_rel(rel_l2(s.get_fields(), traj[-1])) <= 1e-11
