@@ -879,7 +879,12 @@ adj_row_kernel(AdjArgs<T> a) {
   const RowMap<T, G::NH, E> rm(t, a.ts, unsigned(team) * unsigned(a.rs));
   const long long rs0 = (long long)row0 * a.rs;
   c2<T>* my = lds + team * G::REGION;
-  constexpr int F = PMAX + 1;
+  // (4096-point float rows from three order parameters read the count all the
+  // same: the guards keep the compiler from loading every field first, scratch
+  // per lane p = 7 872 -> 324 bytes; four steps with their recomputation, 4096 x
+  // 512: p = 4 898 -> 763 us, p = 7 1797 -> 1577, p = 8 2065 -> 1839; FP64 and p = 2 slower)
+  constexpr bool READ_F = sizeof(T) == 4 && NX == 4096 && PMAX > 2;
+  const int F = READ_F ? a.F : PMAX + 1;
   const int p = F - 1;
   Twiddles<T, G::NH, E> tws;
   tws.load(t, a.twx, 2);

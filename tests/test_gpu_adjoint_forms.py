@@ -1,6 +1,7 @@
 """GPU parity of the adjoint row pass's forms (k_adj.inc) at the lines between
 them: 1024-point float rows of every order-parameter count that has a
-work-group of its own, 512-point double rows with eight, and the last row
+work-group of its own, 4096-point float rows on both sides of the count read at
+run time, 512-point double rows with eight, and the last row
 count of the form for few rows with the first of the regular one.
 
 The loss is half the squared deviation of the fields from their mean, whose
@@ -18,6 +19,7 @@ from parity_util import DISTINCT, announce, fp32_rounded, gpu_or_fail
 pytestmark = pytest.mark.gpu
 
 SHAPES = [(2, (1024, 8), p, "f32") for p in range(1, 9)] + [(2, (1024, 128), 5, "f32")]
+SHAPES += [(2, (4096, 8), p, "f32") for p in (2, 3, 7, 8)]
 SHAPES += [(2, (512, n), 8, "f64") for n in (8, 64)]
 SHAPES += [(2, (256, n), 1, "f64") for n in (512, 1024)] + [(3, (32, 32, 64), 6, "f64"), (3, (8, 128, 256), 2, "f64")]
 

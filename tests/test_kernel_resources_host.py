@@ -53,3 +53,11 @@ def test_wave_adjoint_stays_in_registers(kernels):
     adj = {n: k[".private_segment_fixed_size"] for n, k in kernels.items() if "adjrow_kernel" in n}
     assert len(adj) > 100
     assert {n: b for n, b in adj.items() if b > 64} == {}
+
+
+def test_register_adjoint_float_rows(kernels):
+    """The register form on 4096-point float rows: scratch no larger than with
+    the order-parameter count read at run time (eight: 452 bytes)."""
+    adj = {n: k[".private_segment_fixed_size"] for n, k in kernels.items() if "adj_row_kernelIfLi4096" in n}
+    assert len(adj) == 8
+    assert {n: b for n, b in adj.items() if b > 512} == {}
