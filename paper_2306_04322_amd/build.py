@@ -32,8 +32,9 @@ CFLAGS = ["--offload-arch=" + ARCH, "-O3", "-std=c++17", "-fPIC", "-fno-gpu-rdc"
           "-I" + os.path.join(ROOT, "include"), "-Wno-unused-result"]
 
 
-# The files the FP32 FS row and column kernels are compiled from.
-FS_F32_KERNEL_SOURCES = ["pf_fe.h", "pf_fft.h", "pf_kernels.h", "pf_launch.h",
+# The files the FP32 FS row and column kernels are compiled from, and the rules
+# that choose what they are launched on.
+FS_F32_KERNEL_SOURCES = ["pf_fe.h", "pf_fft.h", "pf_kernels.h", "pf_launch.h", "pf_layout.h",
                          "k_row.inc", "k_col.inc", "k_col_f32.hip"] + ROW_F32
 
 
