@@ -131,14 +131,13 @@ __device__ __forceinline__ void lap_vec3(const T* __restrict__ v, const FdVec<T,
 }
 
 // First point of this thread's vector.  Work-groups are dealt to the eight
-// XCDs round-robin.  With `bands` set (the launch then rounds the group count
-// up to a multiple of 8) XCD x instead takes the x-th contiguous eighth of
-// the grid, so the neighbour rows or planes a group reads were mostly
-// brought into that XCD's L2 by its neighbouring groups.
+// XCDs round-robin; XCD x takes the x-th contiguous eighth of the grid (the
+// launch rounds the group count up to a multiple of 8), so the neighbour rows
+// or planes a group reads were mostly brought into that XCD's L2 by its
+// neighbouring groups.
 template <int V>
-__device__ __forceinline__ long long fd_first_point(int bands) {
-  unsigned b = blockIdx.x;
-  if (bands) b = (b & 7u) * (gridDim.x >> 3) + (b >> 3);
+__device__ __forceinline__ long long fd_first_point() {
+  const unsigned b = (blockIdx.x & 7u) * (gridDim.x >> 3) + (blockIdx.x >> 3);
   return ((long long)b * blockDim.x + threadIdx.x) * V;
 }
 
@@ -146,8 +145,8 @@ __device__ __forceinline__ long long fd_first_point(int bands) {
 // FIXF: all PMAX order parameters in use (p fixed at compile time), as in
 // the mu kernels below.
 template <typename T, int PMAX, int V, bool FIXF = false>
-__global__ void __launch_bounds__(256) fd_mu_kernel(FdArgs<T> a, int bands) {
-  const long long i0 = fd_first_point<V>(bands);
+__global__ void __launch_bounds__(256) fd_mu_kernel(FdArgs<T> a) {
+  const long long i0 = fd_first_point<V>();
   if (i0 >= a.P) return;
   const NbV n = neighbours_vec<T, V>(a, i0);
   const int p = FIXF ? PMAX : a.F - 1;
@@ -187,8 +186,8 @@ __global__ void __launch_bounds__(256) fd_mu_kernel(FdArgs<T> a, int bands) {
 
 // c' = c + dt M lap(mu)
 template <typename T, int V>
-__global__ void __launch_bounds__(256) fd_c_kernel(FdArgs<T> a, int bands) {
-  const long long i0 = fd_first_point<V>(bands);
+__global__ void __launch_bounds__(256) fd_c_kernel(FdArgs<T> a) {
+  const long long i0 = fd_first_point<V>();
   if (i0 >= a.P) return;
   const NbV n = neighbours_vec<T, V>(a, i0);
   const FdVec<T, V> cm = ld_vec<T, V>(a.mu + i0);
@@ -920,8 +919,7 @@ template <typename T, int PMAX, int V>
 static int fd_go_v(int which, const FdArgs<T>& a, hipStream_t s) {
   const long long nv = a.P / V;  // nx >= 8 is a multiple of V
   const bool full = a.F == PMAX + 1;  // the mu kernel's p fixed at compile time
-  const int bands = fd_bands(a);
-  if (!bands) {
+  if (!fd_bands(a)) {
     const int zb = a.nz < PF_FD_ZB ? a.nz : PF_FD_ZB;  // both powers of two
     // LDS-staged form: tiles of R >= 2 rows that divide Ny, with the plane
     // tiles of all F fields small enough for three work-groups per compute
@@ -949,11 +947,10 @@ static int fd_go_v(int which, const FdArgs<T>& a, hipStream_t s) {
     else hipLaunchKernelGGL((fd_c_z_kernel<T, V>), dim3(grid), dim3(256), 0, s, a, zb);
     return grid;
   }
-  int grid = int((nv + 255) / 256);
-  if (bands) grid = (grid + 7) / 8 * 8;
-  if (which == 0 && full) hipLaunchKernelGGL((fd_mu_kernel<T, PMAX, V, true>), dim3(grid), dim3(256), 0, s, a, bands);
-  else if (which == 0) hipLaunchKernelGGL((fd_mu_kernel<T, PMAX, V>), dim3(grid), dim3(256), 0, s, a, bands);
-  else hipLaunchKernelGGL((fd_c_kernel<T, V>), dim3(grid), dim3(256), 0, s, a, bands);
+  const int grid = int((nv + 255) / 256 + 7) / 8 * 8;
+  if (which == 0 && full) hipLaunchKernelGGL((fd_mu_kernel<T, PMAX, V, true>), dim3(grid), dim3(256), 0, s, a);
+  else if (which == 0) hipLaunchKernelGGL((fd_mu_kernel<T, PMAX, V>), dim3(grid), dim3(256), 0, s, a);
+  else hipLaunchKernelGGL((fd_c_kernel<T, V>), dim3(grid), dim3(256), 0, s, a);
   return grid;
 }
 

@@ -434,11 +434,13 @@ pf_status fd_run(pf_handle* h, double dt, long long nsteps) {
     a.in = cur;
     a.out = nxt;
     int pi = prof_begin(h, PROF_FD);
-    if (fd_fused_launch<T>(h->p, a, h->stream) == 0) {
-      fd_launch<T>(0, h->p, a, h->stream);
-      fd_launch<T>(1, h->p, a, h->stream);
+    int g = fd_fused_launch<T>(h->p, a, h->stream);
+    if (g == 0) {
+      g = fd_launch<T>(0, h->p, a, h->stream);
+      if (g > 0) g = fd_launch<T>(1, h->p, a, h->stream);
     }
     prof_end(h, pi);
+    if (g < 0) return fail(PF_ERR_UNSUPPORTED, "FD step: unsupported order-parameter count");
     PF_TRY(check_launch("FD step"));
     T* t = cur;
     cur = nxt;
