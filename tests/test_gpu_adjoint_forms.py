@@ -46,3 +46,11 @@ def test_adjoint_form(ndim, n, p, prec):
     print("lambda", err, "parameters", perr, rpar)
     assert err <= (1e-10 if prec == "f64" else 1e-4)
     assert perr <= (1e-9 if prec == "f64" else 1e-3)
+
+
+@pytest.mark.parametrize("n,p", [((8, 8, 8), 8), ((8, 16, 8), 3), ((32, 32, 16), 4), ((64, 16, 64), 2), ((8, 32, 64), 5),
+                                 ((8, 512, 8), 1), ((16, 128, 32), 7)])
+def test_one_pass_axes_parameters_fp32(n, p):
+    """The parameter gradients in FP32 on 3D grids whose strided axes go in
+    one pass."""
+    test_adjoint_form(3, n, p, "f32")
