@@ -180,8 +180,9 @@ pf_status pf_profile_read(pf_handle* h, int32_t kernel_class, int64_t* count, do
 
 /* Time one pass of the steady-state FS step on its own: `pass` 0 = the row
  * pass (inverse x transform, free-energy derivative, forward x transform),
- * 1 = the k-space update pass (the column pass in 2D; the z-update pass in
- * 3D).  Launches it `reps` times back to back on the handle's stream
+ * 1 = the k-space update pass (the column pass in 2D; in 3D the z-update
+ * pass, or on grids with small (y, z) planes the one pass over both strided
+ * axes, with the y transforms in it).  Launches it `reps` times back to back on the handle's stream
  * between two events, after one untimed launch, and returns the average
  * milliseconds per launch in *avg_ms (synchronises).  Reads and rewrites
  * the step's intermediate buffers in the workspace, so call it after

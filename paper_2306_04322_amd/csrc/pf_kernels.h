@@ -8,9 +8,11 @@
 //                 along y.  Row-major: koff(kx) = kx, rs = Sx (a 128-byte
 //                 multiple).  Tiled (2D with long columns, 3D with small
 //                 planes): tiles of KTile columns (32 bytes) one after the
-//                 other, each [Nz][Ny][KTile], so a column work-group reads
-//                 and writes contiguous memory and a row work-group of R rows
-//                 pieces of 32 R bytes.
+//                 other, each [Nz][Ny][KTile], so a column work-group that
+//                 takes a tile's columns reads and writes contiguous memory
+//                 (from 2048 points it takes half of them, 16 bytes of each
+//                 32, and its neighbour the rest) and a row work-group of R
+//                 rows pieces of 32 R bytes.
 // A "row" is one (z, y) line along x; rows = Ny * Nz.  Keeping the Nyquist
 // column apart lets the strided passes cover kx < Nx/2 with full tiles and
 // the Nyquist column with a few items that take many outer rows at once

@@ -1,5 +1,5 @@
 """GPU parity at the lines between the forms that the launchers choose from
-(k_row.inc, pfspec.hip), where no other test reaches both sides: FS steps in
+(k_row.inc, pf_layout.h), where no other test reaches both sides: FS steps in
 calls of one and of several steps, and the spectral energy.
 
 Tolerances as for the same checks on other shapes: FS FP64 1e-11, FP32 2e-5
